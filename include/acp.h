@@ -342,8 +342,8 @@ enum {
     ACP_K_ROWNORM = 0,  /* Q/K squared row-norm maxima          */
     ACP_K_PLAN = 1,     /* cumsum, threshold, boundary search   */
     ACP_K_FWD = 2,      /* attention forward                    */
-    ACP_K_DSUM = 3,     /* rowdot(dO, O) (float32 path; the bf16
-                           dQ pass forms it itself)              */
+    ACP_K_DSUM = 3,     /* not launched: the dQ pass forms
+                           rowdot(dO, O) itself                  */
     ACP_K_DQ = 4,       /* dQ and row sums of dS                */
     ACP_K_DKDV = 5,     /* dK, dV and column sums of dS         */
     ACP_K_DLOGF = 6,    /* reverse cumulative sum -> dlog f     */

@@ -20,7 +20,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libacp.so")
 BUILD_DIR = os.path.join(PKG, "_build")
 
-SOURCES = ["acp_api.cpp", "acp_plan.hip", "fox_fwd.hip", "fox_bwd.hip", "fox_bwd_mfma.hip",
+SOURCES = ["acp_api.cpp", "acp_plan.hip", "fox_fwd.hip", "fox_bwd.hip", "fox_bwd_mfma.hip", "fox_f32.hip",
            "acp_decode.hip", "acp_project.hip", "acp_noalloc.hip", "acp_gate.hip"]
 
 COMMON = [

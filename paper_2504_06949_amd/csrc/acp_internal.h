@@ -83,7 +83,7 @@ struct BwdArgs {
     const float* lse2;
     const int* sched_q;       // query-block schedule (dQ pass)
     const int* sched_k;       // key-block schedule (dK/dV pass)
-    float* dsum;              // Delta (float32 path), then Delta' from the dQ pass
+    float* dsum;              // Delta' from the dQ pass
     float* rowsum;
     float* colsum;
     void* dQ;
@@ -161,6 +161,9 @@ hipError_t launch_fwd(const FwdArgs& a, hipStream_t s);
 hipError_t launch_bwd(const BwdArgs& a, hipStream_t s);
 hipError_t launch_dq_bf16(const BwdArgs& a, hipStream_t s);
 hipError_t launch_dkdv_bf16(const BwdArgs& a, hipStream_t s);
+hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t s);
+hipError_t launch_dq_f32(const BwdArgs& a, hipStream_t s);
+hipError_t launch_dkdv_f32(const BwdArgs& a, hipStream_t s);
 hipError_t launch_qk_project(const ProjectArgs& a, hipStream_t s);
 size_t decode_partials_floats(int BH, int C, int d);
 hipError_t launch_decode_init(const DecodeInitArgs& a, hipStream_t s);

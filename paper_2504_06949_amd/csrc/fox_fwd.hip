@@ -396,72 +396,6 @@ void fwd_bf16_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// fp32 path: plain VALU arithmetic, one thread per query, 64 queries (one
-// pruning row) per workgroup; K/V tiles staged in LDS; online maximum.  The
-// decay is split at R = c of the block's first query off the diagonal and
-// formed per entry on it, as in the bf16 path.
-// ---------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(64) void fwd_f32_kernel(
-    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
-    const float* __restrict__ cg, const int* __restrict__ row_start,
-    float* __restrict__ O, float* __restrict__ lse,
-    float* __restrict__ lse2, int L, int M, float kscale) {
-    __shared__ float ks[64 * D];
-    __shared__ float vs[64 * D];
-    __shared__ float nc[64];   // (R - c_j) log2(e), or c_j on the diagonal tile
-    const int bh = blockIdx.x / M, m = blockIdx.x % M, t = threadIdx.x;
-    const size_t head = (size_t)bh * L;
-    const int query = 64 * m + t;
-    const float rref = cg[head + 64 * m];
-    const float ci = cg[head + query];
-    const float row = (ci - rref) * kLog2e;
-    float q[D], acc[D];
-#pragma unroll
-    for (int k = 0; k < D; ++k) { q[k] = Q[(head + query) * D + k]; acc[k] = 0.f; }
-    float mrun = -INFINITY, lrun = 0.f;
-    const int n0 = row_start[(size_t)bh * M + m];
-    for (int n = n0; n <= m; ++n) {
-        __syncthreads();
-        for (int i = t; i < 64 * D; i += 64) {
-            ks[i] = K[(head + 64 * n) * D + i];
-            vs[i] = V[(head + 64 * n) * D + i];
-        }
-        const float cj = cg[head + 64 * n + t];
-        nc[t] = n == m ? cj : (rref - cj) * kLog2e;
-        __syncthreads();
-        const int jmax = (n == m) ? t : 63;
-        for (int j = 0; j <= jmax; ++j) {
-            float s = 0.f;
-#pragma unroll
-            for (int k = 0; k < D; ++k) s = __builtin_fmaf(q[k], ks[j * D + k], s);
-            const float y = n == m ? __builtin_fmaf(s, kscale, (ci - nc[j]) * kLog2e)
-                                   : __builtin_fmaf(s, kscale, nc[j]) + row;
-            if (y > mrun) {
-                const float alpha = fast_exp2(mrun - y);
-                lrun *= alpha;
-#pragma unroll
-                for (int k = 0; k < D; ++k) acc[k] *= alpha;
-                mrun = y;
-            }
-            const float p = fast_exp2(y - mrun);
-            lrun += p;
-#pragma unroll
-            for (int k = 0; k < D; ++k) acc[k] = __builtin_fmaf(p, vs[j * D + k], acc[k]);
-        }
-    }
-    const float inv = 1.0f / lrun;
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-        const float o = acc[k] * inv;
-        O[(head + query) * D + k] = o;
-    }
-    const float l2 = mrun + fast_log2(lrun);
-    lse2[head + query] = l2;
-    lse[head + query] = l2 * kLn2;
-}
-
-// ---------------------------------------------------------------------------
 template <int D>
 static void launch_fwd_bf16(const FwdArgs& a, int M, float kscale, hipStream_t s) {
     const int BH = a.B * a.H;
@@ -474,23 +408,17 @@ static void launch_fwd_bf16(const FwdArgs& a, int M, float kscale, hipStream_t s
 }
 
 hipError_t launch_fwd(const FwdArgs& a, hipStream_t s) {
-    const int BH = a.B * a.H, M = a.L / 64;
+    const int M = a.L / 64;
     const float kscale = kLog2e / sqrtf((float)a.d);
     trace_begin(ACP_K_FWD, s);
+    hipError_t e;
     if (a.bf16) {
         if (a.d == 64) launch_fwd_bf16<64>(a, M, kscale, s);
         else launch_fwd_bf16<128>(a, M, kscale, s);
+        e = hipGetLastError();
     } else {
-        if (a.d == 64)
-            hipLaunchKernelGGL(fwd_f32_kernel<64>, dim3(BH * M), dim3(64), 0, s,
-                               (const float*)a.Q, (const float*)a.K, (const float*)a.V, a.c,
-                               a.row_start, (float*)a.O, a.lse, a.lse2, a.L, M, kscale);
-        else
-            hipLaunchKernelGGL(fwd_f32_kernel<128>, dim3(BH * M), dim3(64), 0, s,
-                               (const float*)a.Q, (const float*)a.K, (const float*)a.V, a.c,
-                               a.row_start, (float*)a.O, a.lse, a.lse2, a.L, M, kscale);
+        e = launch_fwd_f32(a, s);
     }
-    const hipError_t e = hipGetLastError();
     trace_end(ACP_K_FWD, s);
     return e;
 }

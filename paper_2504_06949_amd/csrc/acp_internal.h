@@ -142,6 +142,39 @@ struct DecodeArgs {
     float* lse;               // [B*H]
 };
 
+// Key groups (query groups in the dK/dV pass) per workgroup of the bf16 attention
+// kernels: G groups of 4 waves share a 128-row block, each taking every G-th tile of
+// the other operand, so that a block's serial chain of up to 2 nb tiles gets G times
+// shorter when the blocks (nblocks of them, nb per head) are too few to fill the chip.
+// The price is that a CU's waves meet at one barrier per step instead of running as
+// independent workgroups, so one group stays the better form as soon as there are
+// blocks enough.  Measured, us with one group -> with G:
+//   forward, d = 64 (4 workgroups per CU), G = 2: 512 blocks of nb = 32 66 -> 55, 768 of
+//     64 137 -> 116, 1024 of 32 81 -> 77; but 768 of 8 27 -> 32, 1280 of 32 92 -> 97,
+//     1344 of 56 152 -> 157.  G = 4: 205 of 41 73 -> 51 (G = 2: 57), 192 of 16 35 -> 28
+//     (29); but 512 of 32 56 (55), 768 of 64 126 (116).
+//   forward, d = 128 (2 per CU), G = 2: 512 of 32 105 -> 82, 512 of 64 193 -> 139; but 768
+//     of 32 111 -> 111, 1024 of 32 127 -> 143.
+//   dQ, d = 64 (3 per CU), G = 3: 96 of 8 25 -> 24, 192 of 16 42 -> 35, 512 of 32 82 -> 71,
+//     768 of 64 158 -> 143; but 384 of 8 30 -> 33, 1024 of 32 101 -> 121.
+//   dQ, d = 128, G = 2: 256 of 8 40 -> 35, 512 of 32 131 -> 106, 512 of 64 244 -> 175; but
+//     768 of 32 142 -> 141, 1024 of 32 175 -> 196.
+//   dK/dV, d = 64, G = 3: 96 of 8 30 -> 25, 192 of 16 52 -> 38, 512 of 32 102 -> 80, 768 of
+//     64 207 -> 160; but 1024 of 32 130 -> 135, 1344 of 56 233 -> 253.  (At d = 128 its
+//     LDS holds one group of 8 waves.)
+// Below 8 blocks per head the prologue and the merge outweigh the shorter chain.
+inline int fwd_groups(int d, int nblocks, int nb) {
+    if (nb < 8) return 1;
+    if (d == 128) return nblocks <= 512 ? 2 : 1;
+    if (nblocks <= 256 && nb >= 16) return 4;
+    return nblocks <= 1024 && nblocks <= 32 * nb ? 2 : 1;
+}
+inline int bwd_groups(int d, int nblocks, int nb) {
+    if (nb < 8) return 1;
+    if (d == 128) return nblocks <= 512 ? 2 : 1;
+    return nblocks <= 768 && nblocks <= 16 * nb ? 3 : 1;
+}
+
 // Records the message that acp_last_error() returns and passes the status on.
 acp_status set_error(acp_status s, const char* fmt, ...);
 

@@ -11,7 +11,8 @@
 // part that belongs to the wave's own rows goes into the MFMA accumulator start
 // together with -L_i, the other part is a bias held per column.
 //
-// Both passes use 4 waves of 32 rows (two 64-row pruning blocks per workgroup),
+// Both passes use groups of 4 waves of 32 rows (two 64-row pruning blocks per
+// workgroup; one group, or several that share out the tiles: bwd_groups),
 // so a pruned or non-causal tile is skipped wave-uniformly, and work through
 // each 64-row tile of the other operand in two halves of 32 to keep register
 // pressure low; at d = 64 both fit 168 VGPRs, i.e. three waves per SIMD.  Tiles
@@ -34,16 +35,18 @@ constexpr int kBwdRows = 128;
 // in the B-operand layout of dQ^T = K^T dS^T.  The A-operand rows are read in
 // the order krow = 32 h + 8 (r / 4) + 4 t + r % 4 (half h, subtile t).
 // ---------------------------------------------------------------------------
+// What one key group of 4 waves works on; a workgroup has G of them, which take
+// every G-th key tile and add their sums at the end.
 template <int D>
-struct alignas(1024) DqSmem {
+struct alignas(1024) DqTiles {
     unsigned char k[2][128 * D];   // 64 x D bf16 tiles (see tile_off)
     unsigned char v[2][128 * D];
     float kb[2][2][64];            // key bias (R - c_j) log2(e), per query block of the workgroup
     float kc[2][64];               // c_j (diagonal tiles)
 };
 
-template <int D>
-__global__ __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
+template <int D, int G>
+__global__ __launch_bounds__(kBwdThreads * G) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
 void dq_bf16_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
     const __bf16* __restrict__ O, const __bf16* __restrict__ dO, const float* __restrict__ cg,
@@ -53,13 +56,16 @@ void dq_bf16_kernel(
     float qscale) {
     constexpr int NDS = D / 32;
     constexpr int NDT = D / 16;
-    __shared__ DqSmem<D> sm;
+    __shared__ DqTiles<D> smem[G];
 
     const int item = sched[xcd_logical_id(blockIdx.x, nblocks)];   // bh * nqb + query block
     const int bh = item / nqb;
     const int qb = item % nqb;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // wave w of its key group: thread tid of the group's 256
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int grp = G == 1 ? 0 : wave >> 2, w = G == 1 ? wave : wave & 3;
+    const int tid = G == 1 ? (int)threadIdx.x : (int)threadIdx.x & (kBwdThreads - 1), lane = tid & 63;
+    DqTiles<D>& sm = smem[grp];
     const int g = lane >> 4, r16 = lane & 15;
     const int q0 = qb * kBwdRows;
     const int wq0 = q0 + 32 * w;
@@ -262,12 +268,14 @@ void dq_bf16_kernel(
         }
     };
 
-    // tile n_lo in LDS and published; tile n_lo + 1 on its way
-    put_kb(issue(n_lo, 0), 0);
+    // Group grp takes tiles n_lo + grp, n_lo + grp + G, ...; all groups go through
+    // the same steps and barriers.  The group's first tile in LDS and published, its
+    // second on its way.
+    if (G == 1 || n_lo + grp <= n_hi) put_kb(issue(n_lo + grp, 0), 0);
     wait_vmcnt0();
     __syncthreads();
     float4 cnext = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (n_lo < n_hi) cnext = issue(n_lo + 1, 1);
+    if (n_lo + grp + G <= n_hi) cnext = issue(n_lo + grp + G, 1);
     int buf = 0;
     if constexpr (D == 64) {
     auto step = [&](auto mask_tag, int n) __attribute__((always_inline)) {
@@ -283,22 +291,23 @@ void dq_bf16_kernel(
                 phase_c(rc, y);
             }
         }
-        if (n < n_hi) put_kb(cnext, buf ^ 1);
-        // tile n + 1 has landed and every wave's reads of tile n are complete
+        if (n + G <= n_hi) put_kb(cnext, buf ^ 1);
+        // tile n + G has landed and every wave's reads of tile n are complete
         wait_vmcnt0_lgkmcnt0();
         __syncthreads();
-        const bool more = n + 1 < n_hi;
-        if (more && tid < 16) cnext = *reinterpret_cast<const float4*>(cg + head + 64 * (n + 2) + 4 * tid);
-        if (more) dma.issue(sm.k[buf], K + (head + (size_t)64 * (n + 2)) * D, w);
-        if (more) dma.issue(sm.v[buf], V + (head + (size_t)64 * (n + 2)) * D, w);
+        const bool more = n + 2 * G <= n_hi;
+        if (more && tid < 16)
+            cnext = *reinterpret_cast<const float4*>(cg + head + 64 * (n + 2 * G) + 4 * tid);
+        if (more) dma.issue(sm.k[buf], K + (head + (size_t)64 * (n + 2 * G)) * D, w);
+        if (more) dma.issue(sm.v[buf], V + (head + (size_t)64 * (n + 2 * G)) * D, w);
         buf ^= 1;
     };
     // The diagonal tiles (m0 for waves 0-1, m0 + 1 = n_hi for waves 2-3) are the
-    // last two and go through the masking variant.
+    // last two; a step that holds one goes through the masking variant.
     const int n_mask = max(n_lo, n_hi - 1);
-    int n = n_lo;
-    for (; n < n_mask; ++n) step(std::false_type{}, n);
-    for (; n <= n_hi; ++n) step(std::true_type{}, n);
+    int n = n_lo;   // the first group's tile
+    for (; n + G - 1 < n_mask; n += G) step(std::false_type{}, n + grp);
+    for (; n <= n_hi; n += G) step(std::true_type{}, n + grp);
     } else {
     // d = 128: phase A is split in two, S^T with the key rows and dP^T with the
     // value rows, each read just before its MFMAs, so that no more than one
@@ -391,22 +400,54 @@ void dq_bf16_kernel(
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (n < n_hi) put_kb(cnext, buf ^ 1);
-        // tile n + 1 has landed and every wave's reads of tile n are complete
+        if (n + G <= n_hi) put_kb(cnext, buf ^ 1);
+        // tile n + G has landed and every wave's reads of tile n are complete
         wait_vmcnt0_lgkmcnt0();
         __syncthreads();
-        const bool more = n + 1 < n_hi;
-        if (more && tid < 16) cnext = *reinterpret_cast<const float4*>(cg + head + 64 * (n + 2) + 4 * tid);
-        if (more) dma.issue(sm.k[buf], K + (head + (size_t)64 * (n + 2)) * D, w);
-        if (more) dma.issue(sm.v[buf], V + (head + (size_t)64 * (n + 2)) * D, w);
+        const bool more = n + 2 * G <= n_hi;
+        if (more && tid < 16)
+            cnext = *reinterpret_cast<const float4*>(cg + head + 64 * (n + 2 * G) + 4 * tid);
+        if (more) dma.issue(sm.k[buf], K + (head + (size_t)64 * (n + 2 * G)) * D, w);
+        if (more) dma.issue(sm.v[buf], V + (head + (size_t)64 * (n + 2 * G)) * D, w);
         buf ^= 1;
     };
     const int n_mask = max(n_lo, n_hi - 1);
-    int n = n_lo;
-    for (; n < n_mask; ++n) step(std::false_type{}, n);
-    for (; n <= n_hi; ++n) step(std::true_type{}, n);
+    int n = n_lo;   // the first group's tile
+    for (; n + G - 1 < n_mask; n += G) step(std::false_type{}, n + grp);
+    for (; n <= n_hi; n += G) step(std::true_type{}, n + grp);
     }
 
+    if constexpr (G > 1) {
+        // The other groups' sums go to the first through their tiles' LDS, no longer
+        // read (the last step ended with a barrier): dQ^T lane-major, sum_j dS per query.
+        static_assert(sizeof(sm.k) + sizeof(sm.v) >= 4 * 2 * NDT * 64 * sizeof(f32x4), "dQ staging");
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) {
+            sds[qt] += __shfl_xor(sds[qt], 16);
+            sds[qt] += __shfl_xor(sds[qt], 32);
+        }
+        if (grp > 0 && wave_on) {
+            f32x4* so = reinterpret_cast<f32x4*>(&sm.k[0][0]);
+#pragma unroll
+            for (int qt = 0; qt < 2; ++qt) {
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt) so[((w * 2 + qt) * NDT + dt) * 64 + lane] = acc[qt][dt];
+                if (g == 0) (&sm.kb[0][0][0])[32 * w + 16 * qt + r16] = sds[qt];
+            }
+        }
+        lds_barrier();
+        if (grp > 0) return;
+#pragma unroll
+        for (int j = 1; j < G; ++j) {
+            const f32x4* so = reinterpret_cast<const f32x4*>(&smem[j].k[0][0]);
+#pragma unroll
+            for (int qt = 0; qt < 2; ++qt) {
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt) acc[qt][dt] += so[((w * 2 + qt) * NDT + dt) * 64 + lane];
+                sds[qt] += (&smem[j].kb[0][0][0])[32 * w + 16 * qt + r16];
+            }
+        }
+    }
     if (!wave_on) return;
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
@@ -427,8 +468,10 @@ void dq_bf16_kernel(
         // to that rounding, as they are exactly for any softmax (its value does not
         // change when a whole row of logits is shifted).
         float a = sds[qt];
-        a += __shfl_xor(a, 16);
-        a += __shfl_xor(a, 32);
+        if constexpr (G == 1) {
+            a += __shfl_xor(a, 16);
+            a += __shfl_xor(a, 32);
+        }
         if (g == 0) {
             dsum[head + query] = a - dinit[qt][0];
             rowsum[head + query] = 0.f;
@@ -455,22 +498,29 @@ struct DkvShape {
     static constexpr bool kVinLds = D == 128;         // V rows from LDS (else registers)
 };
 
+// What one query group works on: the workgroup has G of them (d = 64 only), which
+// take every G-th query tile and add their sums at the end.
 template <int D>
-struct alignas(1024) DkvSmem {
+struct alignas(1024) DkvTiles {
     unsigned char q[2][128 * D];   // 64 x D bf16 tiles (see tile_off)
     unsigned char o[2][128 * D];   // dO
-    unsigned char k[2][128 * D];   // the workgroup's 128 keys (two tiles)
-    // d = 128: their values (the B operand of dP)
-    unsigned char v[DkvShape<D>::kVinLds ? 2 : 1][DkvShape<D>::kVinLds ? 128 * D : 16];
     float la[2][2][64];            // a_i / k',  a_i = (c_i - R) log2(e) - L_i, per key block
     float ll[2][64];               // -L_i / k' (diagonal tiles)
     float lc[2][64];               // c_i (diagonal tiles)
     float dl[2][64];               // -Delta'_i
-    float kc[128];                 // c_j of the workgroup's keys (diagonal tiles)
 };
 
-template <int D>
-__global__ __launch_bounds__(64 * DkvShape<D>::NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
+template <int D, int G>
+struct alignas(1024) DkvSmem {
+    unsigned char k[2][128 * D];   // the workgroup's 128 keys (two tiles)
+    // d = 128: their values (the B operand of dP)
+    unsigned char v[DkvShape<D>::kVinLds ? 2 : 1][DkvShape<D>::kVinLds ? 128 * D : 16];
+    float kc[128];                 // c_j of the workgroup's keys (diagonal tiles)
+    DkvTiles<D> grp[G];
+};
+
+template <int D, int G>
+__global__ __launch_bounds__(64 * DkvShape<D>::NW * G) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
 void dkdv_bf16_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
     const __bf16* __restrict__ dO, const float* __restrict__ cg,
@@ -482,13 +532,17 @@ void dkdv_bf16_kernel(
     constexpr int NDT = D / 16;
     constexpr int QSPLIT = DkvShape<D>::QSPLIT, NW = DkvShape<D>::NW;
     constexpr bool kVinLds = DkvShape<D>::kVinLds;
-    __shared__ DkvSmem<D> sm;
+    static_assert(G == 1 || QSPLIT == 1, "query groups at d = 64 only");
+    __shared__ DkvSmem<D, G> sg;
 
     const int item = sched[xcd_logical_id(blockIdx.x, nblocks)];   // bh * nkb + key block
     const int bh = item / nkb;
     const int kb = item % nkb;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // wave w of its query group: thread tid of the group's 64 NW
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int grp = G == 1 ? 0 : wave / NW, w = G == 1 ? wave : wave % NW;
+    const int tid = G == 1 ? (int)threadIdx.x : (int)threadIdx.x & (64 * NW - 1), lane = tid & 63;
+    DkvTiles<D>& sm = sg.grp[grp];
     const int kg = w & 3;                   // the wave's key group
     const int qh = w >> 2;                  // its query half (d = 128)
     const int wb = kg >> 1;                 // the key group's block in the workgroup
@@ -512,7 +566,7 @@ void dkdv_bf16_kernel(
 
     bf16x8 vf[2][kVinLds ? 1 : NDS];   // d = 64: the wave's V rows
     float nk[2] = {0.f, 0.f};          // (R - c_j) log2(e) of the lane's keys
-    if (tid < 128) sm.kc[tid] = k0 + tid < L ? cg[head + k0 + tid] : 0.f;
+    if (threadIdx.x < 128) sg.kc[tid] = k0 + tid < L ? cg[head + k0 + tid] : 0.f;
     if (wave_on) {
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt) {
@@ -635,7 +689,7 @@ void dkdv_bf16_kernel(
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-            for (int ds = 0; ds < NDS; ++ds) kr[kt][ds] = tile_row8(sm.k[wb], krow + 16 * kt, 32 * ds + 8 * g);
+            for (int ds = 0; ds < NDS; ++ds) kr[kt][ds] = tile_row8(sg.k[wb], krow + 16 * kt, 32 * ds + 8 * g);
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -650,7 +704,7 @@ void dkdv_bf16_kernel(
             for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
                 for (int ds = 0; ds < NDS; ++ds) {
-                    const bf16x8 vr = tile_row8(sm.v[wb], krow + 16 * kt, 32 * ds + 8 * g);
+                    const bf16x8 vr = tile_row8(sg.v[wb], krow + 16 * kt, 32 * ds + 8 * g);
 #pragma unroll
                     for (int t = 0; t < 2; ++t)
                         x.dp[t][kt] = mfma16(rd.b[t][ds], vr, ds == 0 ? rd.di[t] : x.dp[t][kt]);
@@ -679,8 +733,8 @@ void dkdv_bf16_kernel(
             const float4 b = *reinterpret_cast<const float4*>(&sm.lc[buf][32 * h + 8 * g + 4]);
             ci[0] = a.x; ci[1] = a.y; ci[2] = a.z; ci[3] = a.w;
             ci[4] = b.x; ci[5] = b.y; ci[6] = b.z; ci[7] = b.w;
-            ck[0] = sm.kc[32 * kg + r16];
-            ck[1] = sm.kc[32 * kg + 16 + r16];
+            ck[0] = sg.kc[32 * kg + r16];
+            ck[1] = sg.kc[32 * kg + 16 + r16];
         }
         PdS y;
 #pragma unroll
@@ -714,18 +768,20 @@ void dkdv_bf16_kernel(
 
     // The workgroup's K (and at d = 128 V) tiles; when only 64 keys are left, the
     // second block's waves hold none
-    dma.issue(sm.k[0], K + (head + k0) * D, w);
-    if (k0 + 64 < L) dma.issue(sm.k[1], K + (head + k0 + 64) * D, w);
+    if (grp == 0) dma.issue(sg.k[0], K + (head + k0) * D, w);
+    if (grp == 0 && k0 + 64 < L) dma.issue(sg.k[1], K + (head + k0 + 64) * D, w);
     if constexpr (kVinLds) {
-        dma.issue(sm.v[0], V + (head + k0) * D, w);
-        if (k0 + 64 < L) dma.issue(sm.v[1], V + (head + k0 + 64) * D, w);
+        dma.issue(sg.v[0], V + (head + k0) * D, w);
+        if (k0 + 64 < L) dma.issue(sg.v[1], V + (head + k0 + 64) * D, w);
     }
-    // tile m_lo in LDS and published; tile m_lo + 1 on its way
-    put_rows(issue(m_lo, 0), 0);
+    // Group grp takes tiles m_lo + grp, m_lo + grp + G, ...; all groups go through
+    // the same steps and barriers.  The group's first tile in LDS and published, its
+    // second on its way.
+    if (G == 1 || m_lo + grp <= m_hi) put_rows(issue(m_lo + grp, 0), 0);
     wait_vmcnt0();
     __syncthreads();
     float3 rnext = make_float3(0.f, 0.f, 0.f);
-    if (m_lo < m_hi) rnext = issue(m_lo + 1, 1);
+    if (m_lo + grp + G <= m_hi) rnext = issue(m_lo + grp + G, 1);
     int buf = 0;
     auto step = [&](auto mask_tag, int m) __attribute__((always_inline)) {
         const bool act = m >= nw && m <= w_hi;
@@ -753,25 +809,66 @@ void dkdv_bf16_kernel(
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (m < m_hi) put_rows(rnext, buf ^ 1);
-        // tile m + 1 has landed and every wave's reads of tile m are complete
+        if (m + G <= m_hi) put_rows(rnext, buf ^ 1);
+        // tile m + G has landed and every wave's reads of tile m are complete
         wait_vmcnt0_lgkmcnt0();
         __syncthreads();
-        const bool more = m + 1 < m_hi;
+        const bool more = m + 2 * G <= m_hi;
         if (more && tid < 64) {
-            const size_t row = head + 64 * (m + 2) + tid;
+            const size_t row = head + 64 * (m + 2 * G) + tid;
             rnext = make_float3(cg[row], lse2[row], dsum[row]);
         }
-        if (more) dma.issue(sm.q[buf], Q + (head + (size_t)64 * (m + 2)) * D, w);
-        if (more) dma.issue(sm.o[buf], dO + (head + (size_t)64 * (m + 2)) * D, w);
+        if (more) dma.issue(sm.q[buf], Q + (head + (size_t)64 * (m + 2 * G)) * D, w);
+        if (more) dma.issue(sm.o[buf], dO + (head + (size_t)64 * (m + 2 * G)) * D, w);
         buf ^= 1;
     };
     // The first block's waves meet their diagonal tile at m_lo, the second
-    // block's at m_lo + 1; those two tiles go through the masking variant.
+    // block's at m_lo + 1; the steps that hold them go through the masking variant.
     const int m_diag = min(m_lo + 1, m_hi);
-    int m = m_lo;
-    for (; m <= m_diag; ++m) step(std::true_type{}, m);
-    for (; m <= m_hi; ++m) step(std::false_type{}, m);
+    int m = m_lo;   // the first group's tile
+    for (; m <= m_diag; m += G) step(std::true_type{}, m + grp);
+    for (; m <= m_hi; m += G) step(std::false_type{}, m + grp);
+
+    if constexpr (G > 1) {
+        // The other groups' sums go to the first through their tiles' LDS, no longer
+        // read (the last step ended with a barrier): dK, then dV, lane-major, and the
+        // column sums per key.
+        static_assert(sizeof(sm.q) + sizeof(sm.o) >= 4 * 2 * NDT * 64 * sizeof(f32x4), "staging");
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) {
+            csum[kt] += __shfl_xor(csum[kt], 16);
+            csum[kt] += __shfl_xor(csum[kt], 32);
+            if (grp > 0 && g == 0) (&sm.la[0][0][0])[32 * kg + 16 * kt + r16] = csum[kt];
+        }
+        auto hand_over = [&](f32x4 (&a)[2][NDT]) __attribute__((always_inline)) {
+            if (grp > 0) {
+                f32x4* so = reinterpret_cast<f32x4*>(&sm.q[0][0]);
+#pragma unroll
+                for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                    for (int dt = 0; dt < NDT; ++dt) so[((kg * 2 + kt) * NDT + dt) * 64 + lane] = a[kt][dt];
+            }
+            lds_barrier();
+            if (grp == 0) {
+#pragma unroll
+                for (int j = 1; j < G; ++j) {
+                    const f32x4* so = reinterpret_cast<const f32x4*>(&sg.grp[j].q[0][0]);
+#pragma unroll
+                    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                        for (int dt = 0; dt < NDT; ++dt) a[kt][dt] += so[((kg * 2 + kt) * NDT + dt) * 64 + lane];
+                }
+            }
+        };
+        hand_over(dk);
+        lds_barrier();
+        hand_over(dv);
+        if (grp > 0) return;
+#pragma unroll
+        for (int j = 1; j < G; ++j)
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) csum[kt] += (&sg.grp[j].la[0][0][0])[32 * kg + 16 * kt + r16];
+    }
 
     if constexpr (QSPLIT == 2) {
 #pragma unroll
@@ -784,9 +881,9 @@ void dkdv_bf16_kernel(
         // a barrier): dK in the Q and dO tiles, dV in the K and V tiles, lane-major
         // so that the 16-byte accesses do not conflict.
         static_assert(sizeof(sm.q) + sizeof(sm.o) >= 4 * 2 * NDT * 64 * sizeof(f32x4), "dK staging");
-        static_assert(sizeof(sm.k) + sizeof(sm.v) >= 4 * 2 * NDT * 64 * sizeof(f32x4), "dV staging");
+        static_assert(sizeof(sg.k) + sizeof(sg.v) >= 4 * 2 * NDT * 64 * sizeof(f32x4), "dV staging");
         f32x4* sdk = reinterpret_cast<f32x4*>(&sm.q[0][0]);
-        f32x4* sdv = reinterpret_cast<f32x4*>(&sm.k[0][0]);
+        f32x4* sdv = reinterpret_cast<f32x4*>(&sg.k[0][0]);
         if (qh == 1) {
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt) {
@@ -796,7 +893,7 @@ void dkdv_bf16_kernel(
                     sdk[e] = dk[kt][dt];
                     sdv[e] = dv[kt][dt];
                 }
-                if (g == 0) sm.kc[32 * kg + 16 * kt + r16] = csum[kt];
+                if (g == 0) sg.kc[32 * kg + 16 * kt + r16] = csum[kt];
             }
         }
         __syncthreads();
@@ -809,7 +906,7 @@ void dkdv_bf16_kernel(
                 dk[kt][dt] += sdk[e];
                 dv[kt][dt] += sdv[e];
             }
-            csum[kt] += sm.kc[32 * kg + 16 * kt + r16];
+            csum[kt] += sg.kc[32 * kg + 16 * kt + r16];
         }
     }
     if (!wave_on) return;
@@ -828,7 +925,7 @@ void dkdv_bf16_kernel(
             *reinterpret_cast<bf16x4*>(dV + off) = bb;
         }
         float c = csum[kt];
-        if constexpr (QSPLIT == 1) {
+        if constexpr (QSPLIT == 1 && G == 1) {
             c += __shfl_xor(c, 16);
             c += __shfl_xor(c, 32);
         }
@@ -837,45 +934,44 @@ void dkdv_bf16_kernel(
 }
 
 // ---------------------------------------------------------------------------
+template <int D, int G>
+static void dq_t(const BwdArgs& a, hipStream_t s) {
+    const int nqb = (a.L + kBwdRows - 1) / kBwdRows, nblocks = a.B * a.H * nqb;
+    hipLaunchKernelGGL((dq_bf16_kernel<D, G>), dim3(nblocks), dim3(kBwdThreads * G), 0, s,
+                       (const __bf16*)a.Q, (const __bf16*)a.K, (const __bf16*)a.V,
+                       (const __bf16*)a.O, (const __bf16*)a.dO, a.c, a.row_start, a.lse2,
+                       a.dsum, (__bf16*)a.dQ, a.rowsum, a.sched_q, a.L, a.L / 64, nqb, nblocks,
+                       kLog2e / sqrtf((float)D), 1.0f / sqrtf((float)D));
+}
+
 hipError_t launch_dq_bf16(const BwdArgs& a, hipStream_t s) {
-    const int BH = a.B * a.H, M = a.L / 64;
-    const float kscale = kLog2e / sqrtf((float)a.d);
-    const float qscale = 1.0f / sqrtf((float)a.d);
-    const int nqb = (a.L + kBwdRows - 1) / kBwdRows;
-    const int nblocks = BH * nqb;
-    if (a.d == 64)
-        hipLaunchKernelGGL(dq_bf16_kernel<64>, dim3(nblocks), dim3(kBwdThreads), 0, s,
-                           (const __bf16*)a.Q, (const __bf16*)a.K, (const __bf16*)a.V,
-                           (const __bf16*)a.O, (const __bf16*)a.dO, a.c, a.row_start, a.lse2,
-                           a.dsum, (__bf16*)a.dQ, a.rowsum, a.sched_q, a.L, M, nqb, nblocks, kscale,
-                           qscale);
-    else
-        hipLaunchKernelGGL(dq_bf16_kernel<128>, dim3(nblocks), dim3(kBwdThreads), 0, s,
-                           (const __bf16*)a.Q, (const __bf16*)a.K, (const __bf16*)a.V,
-                           (const __bf16*)a.O, (const __bf16*)a.dO, a.c, a.row_start, a.lse2,
-                           a.dsum, (__bf16*)a.dQ, a.rowsum, a.sched_q, a.L, M, nqb, nblocks, kscale,
-                           qscale);
+    const int nb = (a.L + kBwdRows - 1) / kBwdRows;
+    const int G = bwd_groups(a.d, a.B * a.H * nb, nb);
+    if (a.d == 64) {
+        if (G == 3) dq_t<64, 3>(a, s);
+        else dq_t<64, 1>(a, s);
+    } else {
+        if (G == 2) dq_t<128, 2>(a, s);
+        else dq_t<128, 1>(a, s);
+    }
     return hipGetLastError();
 }
 
+template <int D, int G>
+static void dkdv_t(const BwdArgs& a, hipStream_t s) {
+    const int nkb = (a.L + kBwdRows - 1) / kBwdRows, nblocks = a.B * a.H * nkb;
+    hipLaunchKernelGGL((dkdv_bf16_kernel<D, G>), dim3(nblocks), dim3(64 * DkvShape<D>::NW * G), 0, s,
+                       (const __bf16*)a.Q, (const __bf16*)a.K, (const __bf16*)a.V,
+                       (const __bf16*)a.dO, a.c, a.col_end, a.lse2, a.dsum, (__bf16*)a.dK,
+                       (__bf16*)a.dV, a.colsum, a.sched_k, a.L, a.L / 64, nkb, nblocks,
+                       kLog2e / sqrtf((float)D), 1.0f / sqrtf((float)D));
+}
+
 hipError_t launch_dkdv_bf16(const BwdArgs& a, hipStream_t s) {
-    const int BH = a.B * a.H, M = a.L / 64;
-    const float kscale = kLog2e / sqrtf((float)a.d);
-    const float qscale = 1.0f / sqrtf((float)a.d);
-    const int nkb = (a.L + kBwdRows - 1) / kBwdRows;
-    const int nblocks = BH * nkb;
-    if (a.d == 64)
-        hipLaunchKernelGGL(dkdv_bf16_kernel<64>, dim3(nblocks), dim3(64 * DkvShape<64>::NW), 0, s,
-                           (const __bf16*)a.Q, (const __bf16*)a.K, (const __bf16*)a.V,
-                           (const __bf16*)a.dO, a.c, a.col_end, a.lse2, a.dsum,
-                           (__bf16*)a.dK, (__bf16*)a.dV, a.colsum, a.sched_k, a.L, M, nkb,
-                           nblocks, kscale, qscale);
-    else
-        hipLaunchKernelGGL(dkdv_bf16_kernel<128>, dim3(nblocks), dim3(64 * DkvShape<128>::NW), 0, s,
-                           (const __bf16*)a.Q, (const __bf16*)a.K, (const __bf16*)a.V,
-                           (const __bf16*)a.dO, a.c, a.col_end, a.lse2, a.dsum,
-                           (__bf16*)a.dK, (__bf16*)a.dV, a.colsum, a.sched_k, a.L, M, nkb,
-                           nblocks, kscale, qscale);
+    const int nb = (a.L + kBwdRows - 1) / kBwdRows;
+    if (a.d == 128) dkdv_t<128, 1>(a, s);
+    else if (bwd_groups(64, a.B * a.H * nb, nb) == 3) dkdv_t<64, 3>(a, s);
+    else dkdv_t<64, 1>(a, s);
     return hipGetLastError();
 }
 

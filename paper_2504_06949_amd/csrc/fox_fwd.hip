@@ -46,7 +46,9 @@ constexpr double kUFixedMax = 32.0;
 // ---------------------------------------------------------------------------
 // bf16 path: v_mfma_f32_16x16x32_bf16, fp32 accumulation.
 //
-// Workgroup = 4 waves = 128 queries (two 64-row pruning blocks); wave w owns
+// Workgroup = 128 queries (two 64-row pruning blocks) and G groups of 4 waves, each
+// group taking every G-th key tile (fwd_groups; one group when the blocks fill the
+// chip); wave w of a group owns
 // 32 queries that all sit in one pruning row, so a pruned or non-causal tile is
 // skipped wave-uniformly and no pruned entry is ever computed.  Key/value tiles
 // of 64 rows are double-buffered in LDS (swizzled panels, filled by DMA loads
@@ -59,26 +61,37 @@ constexpr double kUFixedMax = 32.0;
 // order krow(kt, r) = 32 (kt / 2) + 8 (r / 4) + 4 (kt % 2) + r % 4.
 // ---------------------------------------------------------------------------
 
+// What one key group of 4 waves works on
 template <int D>
-struct alignas(1024) FwdSmem {
+struct alignas(1024) FwdTiles {
     unsigned char k[2][128 * D];   // 64 x D bf16 tiles (see tile_off)
     unsigned char v[2][128 * D];
     float kb[2][2][64];            // key bias (R - c_j) log2(e), per query block of the workgroup
     float kc[2][64];               // c_j (diagonal tiles)
-    float qc[128];                 // c_i of the workgroup's queries (diagonal tiles)
 };
 
-template <int D, bool kFixed>
+template <int D, int G>
+struct alignas(1024) FwdSmem {
+    FwdTiles<D> grp[G];
+    float qc[128];                 // c_i of the workgroup's queries (diagonal tiles)
+    // weight sums (float32, bfloat16) and maximum per query of the groups after the first
+    float part[G > 1 ? G - 1 : 1][G > 1 ? 3 : 1][G > 1 ? 128 : 1];
+};
+
+template <int D, bool kFixed, int G>
 __device__ __forceinline__ void fwd_bf16_body(
-    FwdSmem<D>& sm, int qb, int bh, double u_head,
+    FwdSmem<D, G>& smem, int qb, int bh, double u_head,
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
     const float* __restrict__ cg, const int* __restrict__ row_start,
     __bf16* __restrict__ O, float* __restrict__ lse,
     float* __restrict__ lse2, int L, int M, int nqb, float kscale) {
     constexpr int NDS = D / 32;                     // k-steps over the head dim
     constexpr int NDT = D / 16;                     // output tiles over the head dim
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // wave w of its key group: thread tid of the group's 256
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int grp = G == 1 ? 0 : wave >> 2, w = G == 1 ? wave : wave & 3;
+    const int tid = G == 1 ? (int)threadIdx.x : (int)threadIdx.x & (kFwdThreads - 1), lane = tid & 63;
+    FwdTiles<D>& sm = smem.grp[grp];
     const int g = lane >> 4, r16 = lane & 15;
     const int q0 = qb * kFwdRows;
     const int wq0 = q0 + 32 * w;
@@ -113,7 +126,7 @@ __device__ __forceinline__ void fwd_bf16_body(
             cq[qt] = cg[head + wq0 + 16 * qt + r16];
         }
     }
-    if (tid < 128) sm.qc[tid] = q0 + tid < L ? cg[head + q0 + tid] : 0.f;
+    if (threadIdx.x < 128) smem.qc[tid] = q0 + tid < L ? cg[head + q0 + tid] : 0.f;
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
         const float row = cq[qt] - rw;
@@ -239,7 +252,7 @@ __device__ __forceinline__ void fwd_bf16_body(
             int qk = qk0 + 16 * qt;
             if constexpr (kMask) asm volatile("" : "+v"(qk));
             float ci = 0.f;
-            if constexpr (kMask) ci = sm.qc[32 * w + 16 * qt + r16];
+            if constexpr (kMask) ci = smem.qc[32 * w + 16 * qt + r16];
             // exponent of entry j: the row term is in x.s off the diagonal
             auto expo = [&](int j) __attribute__((always_inline)) {
                 const float bias = kMask ? (ci - nk[j]) * kLog2e : nk[j];
@@ -302,12 +315,14 @@ __device__ __forceinline__ void fwd_bf16_body(
         }
     };
 
-    // tile n_lo in LDS and published; tile n_lo + 1 on its way
-    put_kb(issue(n_lo, 0), 0);
+    // Group grp takes tiles n_lo + grp, n_lo + grp + G, ...; all groups go through
+    // the same steps and barriers.  The group's first tile in LDS and published, its
+    // second on its way.
+    if (G == 1 || n_lo + grp <= n_hi) put_kb(issue(n_lo + grp, 0), 0);
     wait_vmcnt0();
     __syncthreads();
     float4 cnext = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (n_lo < n_hi) cnext = issue(n_lo + 1, 1);
+    if (n_lo + grp + G <= n_hi) cnext = issue(n_lo + grp + G, 1);
     int buf = 0;
     auto step = [&](auto mask_tag, int n) __attribute__((always_inline)) {
         const bool act = n >= w_lo && n <= mw;
@@ -326,29 +341,77 @@ __device__ __forceinline__ void fwd_bf16_body(
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (n < n_hi) put_kb(cnext, buf ^ 1);
-        // tile n + 1 has landed and every wave's reads of tile n are complete
+        if (n + G <= n_hi) put_kb(cnext, buf ^ 1);
+        // tile n + G has landed and every wave's reads of tile n are complete
         wait_vmcnt0_lgkmcnt0();
         __syncthreads();
-        const bool more = n + 1 < n_hi;
-        if (more && tid < 16) cnext = *reinterpret_cast<const float4*>(cg + head + 64 * (n + 2) + 4 * tid);
-        if (more) dma.issue(sm.k[buf], K + (head + (size_t)64 * (n + 2)) * D, w);
-        if (more) dma.issue(sm.v[buf], V + (head + (size_t)64 * (n + 2)) * D, w);
+        const bool more = n + 2 * G <= n_hi;
+        if (more && tid < 16)
+            cnext = *reinterpret_cast<const float4*>(cg + head + 64 * (n + 2 * G) + 4 * tid);
+        if (more) dma.issue(sm.k[buf], K + (head + (size_t)64 * (n + 2 * G)) * D, w);
+        if (more) dma.issue(sm.v[buf], V + (head + (size_t)64 * (n + 2 * G)) * D, w);
         buf ^= 1;
     };
     // The diagonal tiles (m0 for waves 0-1, m0 + 1 for waves 2-3) are the last
-    // two and go through the masking variant.
+    // two; a step that holds one goes through the masking variant.
     const int n_mask = max(n_lo, n_hi - 1);
-    int n = n_lo;
-    for (; n < n_mask; ++n) step(std::false_type{}, n);
-    for (; n <= n_hi; ++n) step(std::true_type{}, n);
+    int n = n_lo;   // the first group's tile
+    for (; n + G - 1 < n_mask; n += G) step(std::false_type{}, n + grp);
+    for (; n <= n_hi; n += G) step(std::true_type{}, n + grp);
 
+    if constexpr (G > 1) {
+        // The other groups hand their partial sums to the first through their tiles'
+        // LDS, no longer read (the last step ended with a barrier): O^T lane-major, the
+        // weight sums and the online maximum per query.
+        static_assert(sizeof(sm.k) + sizeof(sm.v) >= 4 * 2 * NDT * 64 * sizeof(f32x4), "O staging");
+        if (grp > 0 && wave_on) {
+            f32x4* so = reinterpret_cast<f32x4*>(&sm.k[0][0]);
+#pragma unroll
+            for (int qt = 0; qt < 2; ++qt) {
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt) so[((w * 2 + qt) * NDT + dt) * 64 + lane] = acc[qt][dt];
+                lrun[qt] += __shfl_xor(lrun[qt], 16);
+                lrun[qt] += __shfl_xor(lrun[qt], 32);
+                if (g == 0) {
+                    smem.part[grp - 1][0][32 * w + 16 * qt + r16] = lrun[qt];
+                    smem.part[grp - 1][1][32 * w + 16 * qt + r16] = lbf[qt][0];
+                    smem.part[grp - 1][2][32 * w + 16 * qt + r16] = mrun[qt];
+                }
+            }
+        }
+        lds_barrier();
+        if (grp > 0) return;
+    }
     if (!wave_on) return;
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
         float lt = lrun[qt];
         lt += __shfl_xor(lt, 16);
         lt += __shfl_xor(lt, 32);
+        if constexpr (G > 1) {
+#pragma unroll
+            for (int j = 1; j < G; ++j) {
+                const f32x4* so = reinterpret_cast<const f32x4*>(&smem.grp[j].k[0][0]);
+                const int q = 32 * w + 16 * qt + r16;
+                const float lj = smem.part[j - 1][0][q];
+                if constexpr (kFixed) {
+                    lt += lj;
+                    lbf[qt][0] += smem.part[j - 1][1][q];
+#pragma unroll
+                    for (int dt = 0; dt < NDT; ++dt) acc[qt][dt] += so[((w * 2 + qt) * NDT + dt) * 64 + lane];
+                } else {
+                    // (a group without a tile of this query holds nothing: weight 0)
+                    const float mj = smem.part[j - 1][2][q], mnew = fmaxf(mrun[qt], mj);
+                    const float a = mrun[qt] == -INFINITY ? 0.f : fast_exp2(mrun[qt] - mnew);
+                    const float b = mj == -INFINITY ? 0.f : fast_exp2(mj - mnew);
+                    mrun[qt] = mnew;
+                    lt = lt * a + lj * b;
+#pragma unroll
+                    for (int dt = 0; dt < NDT; ++dt)
+                        acc[qt][dt] = acc[qt][dt] * a + so[((w * 2 + qt) * NDT + dt) * 64 + lane] * b;
+                }
+            }
+        }
         // O is normalised by the sum of the weights it was built from: with the
         // fixed stabiliser the largest weight is not 1, and normalising the
         // bfloat16-weighted sum by the float32 sum would leave its rounding in O.
@@ -375,33 +438,33 @@ __device__ __forceinline__ void fwd_bf16_body(
 
 // One launch for both variants: the head's bound picks the body (uniform over
 // the workgroup), and the two bodies share the workgroup's LDS.
-template <int D>
-__global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
+template <int D, int G>
+__global__ __launch_bounds__(kFwdThreads * G) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
 void fwd_bf16_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
     const float* __restrict__ cg, const int* __restrict__ row_start,
     const double* __restrict__ bound_u, const int* __restrict__ sched, __bf16* __restrict__ O,
     float* __restrict__ lse, float* __restrict__ lse2, int L, int M, int nqb, int nblocks,
     float kscale) {
-    __shared__ FwdSmem<D> sm;
+    __shared__ FwdSmem<D, G> sm;
     const int item = sched[xcd_logical_id(blockIdx.x, nblocks)];   // bh * nqb + query block
     const int bh = item / nqb;
     const double u_head = bound_u[bh];
     if (u_head <= kUFixedMax)
-        fwd_bf16_body<D, true>(sm, item % nqb, bh, u_head, Q, K, V, cg, row_start, O, lse, lse2,
+        fwd_bf16_body<D, true, G>(sm, item % nqb, bh, u_head, Q, K, V, cg, row_start, O, lse, lse2,
                                L, M, nqb, kscale);
     else
-        fwd_bf16_body<D, false>(sm, item % nqb, bh, u_head, Q, K, V, cg, row_start, O, lse, lse2,
+        fwd_bf16_body<D, false, G>(sm, item % nqb, bh, u_head, Q, K, V, cg, row_start, O, lse, lse2,
                                 L, M, nqb, kscale);
 }
 
 // ---------------------------------------------------------------------------
-template <int D>
+template <int D, int G>
 static void launch_fwd_bf16(const FwdArgs& a, int M, float kscale, hipStream_t s) {
     const int BH = a.B * a.H;
     const int nqb = (a.L + kFwdRows - 1) / kFwdRows;
     const int nblocks = BH * nqb;
-    hipLaunchKernelGGL((fwd_bf16_kernel<D>), dim3(nblocks), dim3(kFwdThreads), 0, s,
+    hipLaunchKernelGGL((fwd_bf16_kernel<D, G>), dim3(nblocks), dim3(kFwdThreads * G), 0, s,
                        (const __bf16*)a.Q, (const __bf16*)a.K, (const __bf16*)a.V, a.c,
                        a.row_start, a.u, a.sched, (__bf16*)a.O, a.lse, a.lse2, a.L, M, nqb,
                        nblocks, kscale);
@@ -413,8 +476,16 @@ hipError_t launch_fwd(const FwdArgs& a, hipStream_t s) {
     trace_begin(ACP_K_FWD, s);
     hipError_t e;
     if (a.bf16) {
-        if (a.d == 64) launch_fwd_bf16<64>(a, M, kscale, s);
-        else launch_fwd_bf16<128>(a, M, kscale, s);
+        const int nb = (a.L + kFwdRows - 1) / kFwdRows;
+        const int G = fwd_groups(a.d, a.B * a.H * nb, nb);
+        if (a.d == 64) {
+            if (G == 4) launch_fwd_bf16<64, 4>(a, M, kscale, s);
+            else if (G == 2) launch_fwd_bf16<64, 2>(a, M, kscale, s);
+            else launch_fwd_bf16<64, 1>(a, M, kscale, s);
+        } else {
+            if (G == 2) launch_fwd_bf16<128, 2>(a, M, kscale, s);
+            else launch_fwd_bf16<128, 1>(a, M, kscale, s);
+        }
         e = hipGetLastError();
     } else {
         e = launch_fwd_f32(a, s);

@@ -12,8 +12,7 @@
 //   decode_init_kernel  prompt of L0 tokens -> delta, the running cumsum (a
 //                       double-double pair),
 //                       c of the prompt's last C positions, the pointer of query
-//                       L0 - 1
-//   decode_copy_kernel  the prompt's last K/V rows into the ring
+//                       L0 - 1; and the prompt's last K/V rows into the ring
 //   decode_step_kernel  one token: c_t, the pointer advance, query t over its
 //                       kept keys (256 per workgroup, partial softmax sums), and
 //                       the append of k_t, v_t
@@ -44,9 +43,10 @@ size_t decode_partials_floats(int BH, int C, int d) {
 __device__ __forceinline__ int ring(int j, int C) { return j % C; }
 
 // ---------------------------------------------------------------------------
+// The state of head bh after the prompt, by one workgroup.
 template <int D>
-__global__ __launch_bounds__(kPlanThreads) void decode_init_kernel(
-    const float* __restrict__ log_f,
+__device__ __forceinline__ void decode_init_head(
+    int bh, int BH, const float* __restrict__ log_f,
     const float* __restrict__ gamma_q, const float* __restrict__ gamma_k, int H, int L0, int C,
     double log_lmax_over_eps, float* __restrict__ cc,
     double* __restrict__ cs_out, int* __restrict__ ptr_out, double* __restrict__ delta_out,
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kPlanThreads) void decode_init_kernel(
     __shared__ double s_delta;
     __shared__ float s_ct;
 
-    const int bh = blockIdx.x, t = threadIdx.x;
+    const int t = threadIdx.x;
     int flags = 0;
     if (t == 0) {
         // U = (gamma_q gamma_k) sqrt(d), delta = -(2U + log L_max - log eps)
@@ -74,21 +74,32 @@ __global__ __launch_bounds__(kPlanThreads) void decode_init_kernel(
 
     // c = cumsum(log f) of the prompt, each thread a contiguous run (as in stage 1)
     const float* x = log_f + (size_t)bh * L0;
-    const int per = (L0 + kPlanThreads - 1) / kPlanThreads;
-    const int beg = min(t * per, L0), end = min(beg + per, L0);
+    const int per = run_length(L0);
+    const int beg = min(t * per, L0), n = min(beg + per, L0) - beg;
+    const bool vec = (L0 & 3) == 0;   // every head's row is whole float4s
+    float xv[kRunHeld];               // the first batch (all of the run if per <= kRunHeld)
+    load_run(x + beg, 0, n, vec, xv);
     // float64 first, double-double for a head whose sums span 53 bits or more (the
     // rule of the plan kernel, which explains it)
     double local = 0.0, local_abs = 0.0;
     int min_lsb = 1 << 30;
-    for (int i = beg; i < end; ++i) {
-        const float v = x[i];
-        if (!__builtin_isfinite(v)) flags |= 2;
-        else {
-            if (v > 0.0f) flags |= 1;
-            if (v != 0.0f) min_lsb = min(min_lsb, lsb_exp(v));
+    for (int b = 0;;) {
+#pragma unroll
+        for (int i = 0; i < kRunHeld; ++i) {
+            if (b + i < n) {
+                const float v = xv[i];
+                if (!__builtin_isfinite(v)) flags |= 2;
+                else {
+                    if (v > 0.0f) flags |= 1;
+                    if (v != 0.0f) min_lsb = min(min_lsb, lsb_exp(v));
+                }
+                local += (double)v;
+                local_abs += __builtin_fabs((double)v);
+            }
         }
-        local += (double)v;
-        local_abs += __builtin_fabs((double)v);
+        b += kRunHeld;
+        if (b >= n) break;
+        load_run(x + beg, b, n, vec, xv);
     }
     const double incl = block_inclusive_scan(local, s_dbl[0]);
     auto sum = [](double a, double b) { return a + b; };
@@ -103,25 +114,51 @@ __global__ __launch_bounds__(kPlanThreads) void decode_init_kernel(
         wide = top - min_lsb >= 53;
     }
     auto emit = [&](auto run) __attribute__((always_inline)) {
-        for (int i = beg; i < end; ++i) {
-            run = sum_add(run, x[i]);
-            const float cf = sum_f32(run);
-            if (i >= L0 - C) cc[(size_t)bh * C + (i % C)] = cf;
-            if ((i & (kBlock - 1)) == kBlock - 1) s_last[i / kBlock] = cf;
-            if (i == L0 - 1) {
-                double* cs = cs_out + 2 * ((size_t)((L0 - 1) & 1) * gridDim.x + bh);
-                cs[0] = sum_hi(run);
-                cs[1] = sum_lo(run);
-                s_ct = cf;
+        float* ring_c = cc + (size_t)bh * C;
+        for (int b = 0; b < n; b += kRunHeld) {
+            if (per > kRunHeld) load_run(x + beg, b, n, vec, xv);
+            // C and the run's start are multiples of 4, so four positions never wrap
+#pragma unroll
+            for (int q = 0; q < kRunHeld; q += 4) {
+                const int i0 = beg + b + q;
+                const int slot = i0 % C;
+                float4 c4;
+                float* cf = &c4.x;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (b + q + k < n) {
+                        run = sum_add(run, xv[q + k]);
+                        cf[k] = sum_f32(run);
+                        if (i0 + k == L0 - 1) {
+                            double* cs = cs_out + 2 * ((size_t)((L0 - 1) & 1) * BH + bh);
+                            cs[0] = sum_hi(run);
+                            cs[1] = sum_lo(run);
+                            s_ct = cf[k];
+                        }
+                    }
+                }
+                if (b + q + 3 < n && i0 >= L0 - C) {
+                    *reinterpret_cast<float4*>(ring_c + slot) = c4;
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (b + q + k < n && i0 + k >= L0 - C) ring_c[slot + k] = cf[k];
+                }
+                if (b + q + 3 < n && ((i0 + 3) & (kBlock - 1)) == kBlock - 1) s_last[i0 / kBlock] = c4.w;
             }
         }
     };
     if (wide) {
         DD l{0.0, 0.0}, la{0.0, 0.0};
-        for (int i = beg; i < end; ++i) {
-            const double v = (double)x[i];
-            l = dd_add(l, v);
-            la = dd_add(la, __builtin_fabs(v));
+        for (int b = 0; b < n; b += kRunHeld) {
+            if (per > kRunHeld) load_run(x + beg, b, n, vec, xv);
+#pragma unroll
+            for (int i = 0; i < kRunHeld; ++i) {
+                if (b + i < n) {
+                    l = dd_add(l, (double)xv[i]);
+                    la = dd_add(la, __builtin_fabs((double)xv[i]));
+                }
+            }
         }
         const DD inc = block_inclusive_scan_dd(l, s_dbl[0], s_dbl[1]);
         const DD total = block_sum_dd(la, s_dbl2[0], s_dbl2[1]);
@@ -150,31 +187,32 @@ __global__ __launch_bounds__(kPlanThreads) void decode_init_kernel(
         // and the pointer does not go below the block of the oldest position held.
         const int first = L0 - C;
         if (kBlock * lo < first) flags |= 16;
-        ptr_out[(size_t)((L0 - 1) & 1) * gridDim.x + bh] = max(lo, first > 0 ? first / kBlock : 0);
+        ptr_out[(size_t)((L0 - 1) & 1) * BH + bh] = max(lo, first > 0 ? first / kBlock : 0);
         flags_out[bh] = flags;
     }
 }
 
-// The prompt's last min(L0, C) K and V rows into their ring slots: grid
-// (ceil(rows / 64), B*H), each workgroup 64 rows of both tensors, every lane's
-// 16-byte pieces requested before any is stored.
-constexpr int kCopyRows = 64;
+// The prompt's last min(L0, C) K and V rows into their ring slots: kCopyRows rows of
+// both tensors per workgroup, every lane's 16-byte pieces requested before any is
+// stored.
+constexpr int kCopyRows = 4 * 64;
 
 template <typename T, int D>
-__global__ __launch_bounds__(256) void decode_copy_kernel(
-    const T* __restrict__ K, const T* __restrict__ V, int L0, int C, T* __restrict__ Kc,
-    T* __restrict__ Vc) {
+__device__ __forceinline__ void decode_copy_rows(
+    int bh, int chunk, const T* __restrict__ K, const T* __restrict__ V, int L0, int C,
+    T* __restrict__ Kc, T* __restrict__ Vc) {
     constexpr int kVec = 16 / (int)sizeof(T);
-    constexpr int kPerRow = D / kVec;                  // 16-byte pieces per row
-    constexpr int kPer = kCopyRows * kPerRow / 256;    // pieces per thread and tensor
-    const int bh = blockIdx.y, t = threadIdx.x;
+    constexpr int kPerRow = D / kVec;                           // 16-byte pieces per row
+    constexpr int kPer = kCopyRows * kPerRow / kPlanThreads;    // pieces per thread and tensor
+    const int t = threadIdx.x;
     const int j0 = max(0, L0 - C);
-    const int r0 = j0 + blockIdx.x * kCopyRows;
+    const int r0 = j0 + chunk * kCopyRows;
+    const int c0 = r0 % C;   // (kCopyRows can exceed C: a full modulo per row)
     uint4 kv[kPer], vv[kPer];
 #pragma unroll
     for (int p = 0; p < kPer; ++p) {
         // rows past the prompt read its last row again (branch-free)
-        const int i = t + 256 * p, j = min(r0 + i / kPerRow, L0 - 1), e = (i % kPerRow) * kVec;
+        const int i = t + kPlanThreads * p, j = min(r0 + i / kPerRow, L0 - 1), e = (i % kPerRow) * kVec;
         const size_t src = ((size_t)bh * L0 + j) * D + e;
         kv[p] = *reinterpret_cast<const uint4*>(K + src);
         vv[p] = *reinterpret_cast<const uint4*>(V + src);
@@ -183,11 +221,32 @@ __global__ __launch_bounds__(256) void decode_copy_kernel(
 #pragma unroll
     for (int p = 0; p < kPer; ++p) {
         // (a row past the prompt rewrites the last row's slot with the same bytes)
-        const int i = t + 256 * p, j = min(r0 + i / kPerRow, L0 - 1), e = (i % kPerRow) * kVec;
-        const size_t dst = ((size_t)bh * C + (j % C)) * D + e;
+        const int i = t + kPlanThreads * p, j = min(r0 + i / kPerRow, L0 - 1), e = (i % kPerRow) * kVec;
+        const size_t dst = ((size_t)bh * C + (c0 + (j - r0)) % C) * D + e;
         *reinterpret_cast<uint4*>(Kc + dst) = kv[p];
         *reinterpret_cast<uint4*>(Vc + dst) = vv[p];
     }
+}
+
+// One launch for both: workgroups 0 .. B*H - 1 a head's scan each, the others the
+// rows (nothing orders them against each other).  The scans, one workgroup per head
+// and bound by latency, run beside the copy, which the memory bounds: as two
+// launches 8 + 32 us for 96 heads of 4096 tokens, 145 + 567 for 65536 (the scan then
+// read value by value); as one 33 and
+// 607 (event timing; two launches 39 and 711).
+template <typename T, int D>
+__global__ __launch_bounds__(kPlanThreads) void decode_init_kernel(
+    const T* __restrict__ K, const T* __restrict__ V, const float* __restrict__ log_f,
+    const float* __restrict__ gamma_q, const float* __restrict__ gamma_k, int BH, int H, int L0,
+    int C, int nchunks, double log_lmax_over_eps, T* __restrict__ Kc, T* __restrict__ Vc,
+    float* __restrict__ cc, double* __restrict__ cs_out, int* __restrict__ ptr_out,
+    double* __restrict__ delta_out, int* __restrict__ flags_out) {
+    const int b = blockIdx.x;
+    if (b < BH)
+        decode_init_head<D>(b, BH, log_f, gamma_q, gamma_k, H, L0, C, log_lmax_over_eps, cc,
+                            cs_out, ptr_out, delta_out, flags_out);
+    else
+        decode_copy_rows<T, D>((b - BH) / nchunks, (b - BH) % nchunks, K, V, L0, C, Kc, Vc);
 }
 
 // ---------------------------------------------------------------------------
@@ -520,15 +579,11 @@ __global__ __launch_bounds__(THREADS) void decode_combine_kernel(
 // ---------------------------------------------------------------------------
 template <typename T, int D>
 static hipError_t init_t(const DecodeInitArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL((decode_init_kernel<D>), dim3(a.B * a.H), dim3(kPlanThreads), 0, s,
-                       a.log_f, a.gamma_q, a.gamma_k, a.H, a.L0,
-                       a.C, a.log_lmax_over_eps, a.cc, a.cs, a.ptr, a.delta, a.flags);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int rows = min(a.L0, a.C);
-    hipLaunchKernelGGL((decode_copy_kernel<T, D>),
-                       dim3((rows + kCopyRows - 1) / kCopyRows, a.B * a.H), dim3(256), 0, s,
-                       (const T*)a.K, (const T*)a.V, a.L0, a.C, (T*)a.Kc, (T*)a.Vc);
+    const int BH = a.B * a.H, nchunks = (min(a.L0, a.C) + kCopyRows - 1) / kCopyRows;
+    hipLaunchKernelGGL((decode_init_kernel<T, D>), dim3(BH + BH * nchunks), dim3(kPlanThreads), 0, s,
+                       (const T*)a.K, (const T*)a.V, a.log_f, a.gamma_q, a.gamma_k, BH, a.H, a.L0,
+                       a.C, nchunks, a.log_lmax_over_eps, (T*)a.Kc, (T*)a.Vc, a.cc, a.cs, a.ptr,
+                       a.delta, a.flags);
     return hipGetLastError();
 }
 

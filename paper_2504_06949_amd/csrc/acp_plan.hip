@@ -106,9 +106,10 @@ __global__ __launch_bounds__(kNormThreads) void rownorm_max_kernel(
 }
 
 // One workgroup of 1024 threads per (batch, head); each thread owns a contiguous
-// run of log f, read and written as float4s when the run length is a multiple of
-// 4 (at L = 4096 one float4 per thread, so every access is coalesced), and kept
-// in registers up to kPlanHeld values.  Three barriers in all, none of which
+// run of log f, read and written as float4s (at L = 4096 one per thread, so every
+// access is coalesced), kept in registers up to kRunHeld values and read again in
+// batches of that many when it is longer (value by value, each load waited for, a
+// head of 32768 took 64 us).  Three barriers in all, none of which
 // waits for global stores: one round through LDS carries the scan's wave totals
 // together with every reduction (|log f| sum, last-bit position, flags, norm
 // maxima), one publishes the block corners of c, one the first kept blocks.
@@ -116,7 +117,6 @@ __global__ __launch_bounds__(kNormThreads) void rownorm_max_kernel(
 // identical everywhere without another round.  Cross-lane traffic is kept low:
 // the gate flags go through wave ballots, and the norm maxima are reduced only
 // by the waves that hold partials.
-constexpr int kPlanHeld = 16;   // log f values a thread keeps in registers (L <= 16384)
 constexpr int kWideBit = 1 << 16;   // (inside the kernel only) the gated mode needs pairs
 
 __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
@@ -140,23 +140,11 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
     // ---- requests: this thread's run of log f and the norm partials -----------
     const float* x = log_f + (size_t)bh * L;
     float* cw = c_out + (size_t)bh * L;
-    const int per = (L + kPlanThreads - 1) / kPlanThreads;
+    const int per = run_length(L);
     const bool gated = gate != nullptr;   // c in place: no gates to read or scan
     const int beg = min(t * per, L), n = gated ? 0 : min(beg + per, L) - beg;
-    const bool held = per <= kPlanHeld;
-    const bool vec = held && (per & 3) == 0;   // then n is per or 0
-    float xv[kPlanHeld];
-    if (vec) {
-#pragma unroll
-        for (int i = 0; i < kPlanHeld; i += 4) {
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (i < n) v = *reinterpret_cast<const float4*>(x + beg + i);
-            xv[i] = v.x; xv[i + 1] = v.y; xv[i + 2] = v.z; xv[i + 3] = v.w;
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < kPlanHeld; ++i) xv[i] = held && i < n ? x[beg + i] : 0.f;
-    }
+    float xv[kRunHeld];                   // the first batch (all of it if n <= kRunHeld)
+    load_run(x + beg, 0, n, true, xv);
     double mq = 0.0, mk = 0.0;   // squared norms are >= 0; a NaN wins nan_max
     const bool norms = gamma_q == nullptr;
     if (norms) {
@@ -197,12 +185,15 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
             min_lsb = min(min_lsb, g.min_lsb);
             gate_flags |= g.flags;
         }
-    } else if (held) {
-#pragma unroll
-        for (int i = 0; i < kPlanHeld; ++i)
-            if (i < n) take(xv[i]);
     } else {
-        for (int i = 0; i < n; ++i) take(x[beg + i]);
+        for (int b = 0;;) {
+#pragma unroll
+            for (int i = 0; i < kRunHeld; ++i)
+                if (b + i < n) take(xv[i]);
+            b += kRunHeld;
+            if (b >= n) break;
+            load_run(x + beg, b, n, true, xv);
+        }
     }
 
     // ---- one round through LDS --------------------------------------------------------
@@ -287,19 +278,14 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
     DD run_dd{0.0, 0.0};
     if (wide) {
         DD l{0.0, 0.0}, la = gate_abs;
-        if (held) {
+        for (int b = 0; b < n; b += kRunHeld) {
+            if (per > kRunHeld) load_run(x + beg, b, n, true, xv);
 #pragma unroll
-            for (int i = 0; i < kPlanHeld; ++i) {
-                if (i < n) {
+            for (int i = 0; i < kRunHeld; ++i) {
+                if (b + i < n) {
                     l = dd_add(l, (double)xv[i]);
                     la = dd_add(la, __builtin_fabs((double)xv[i]));
                 }
-            }
-        } else {
-            for (int i = 0; i < n; ++i) {
-                const double v = (double)x[beg + i];
-                l = dd_add(l, v);
-                la = dd_add(la, __builtin_fabs(v));
             }
         }
         const DD inc = wave_inclusive_scan_dd(l);
@@ -363,36 +349,21 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
     };
     // run: the exclusive prefix (float64 or a pair), exact when the span check passes
     auto emit = [&](auto run) __attribute__((always_inline)) {
-        if (vec) {
+        for (int b = 0; b < n; b += kRunHeld) {
+            if (per > kRunHeld) load_run(x + beg, b, n, true, xv);
 #pragma unroll
-            for (int i = 0; i < kPlanHeld; i += 4) {
-                if (i < n) {
+            for (int i = 0; i < kRunHeld; i += 4) {
+                if (b + i < n) {
+                    const int j = beg + b + i;        // a multiple of 4
                     float4 cv;
                     run = sum_add(run, xv[i]);     cv.x = sum_f32(run);
                     run = sum_add(run, xv[i + 1]); cv.y = sum_f32(run);
                     run = sum_add(run, xv[i + 2]); cv.z = sum_f32(run);
                     run = sum_add(run, xv[i + 3]); cv.w = sum_f32(run);
-                    *reinterpret_cast<float4*>(cw + beg + i) = cv;
-                    corner(beg + i, cv.x);            // beg + i is a multiple of 4
-                    corner(beg + i + 3, cv.w);
+                    *reinterpret_cast<float4*>(cw + j) = cv;
+                    corner(j, cv.x);
+                    corner(j + 3, cv.w);
                 }
-            }
-        } else if (held) {
-#pragma unroll
-            for (int i = 0; i < kPlanHeld; ++i) {
-                if (i < n) {
-                    run = sum_add(run, xv[i]);
-                    const float cf = sum_f32(run);
-                    cw[beg + i] = cf;
-                    corner(beg + i, cf);
-                }
-            }
-        } else {
-            for (int i = 0; i < n; ++i) {
-                run = sum_add(run, x[beg + i]);
-                const float cf = sum_f32(run);
-                cw[beg + i] = cf;
-                corner(beg + i, cf);
             }
         }
     };

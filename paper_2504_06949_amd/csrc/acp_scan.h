@@ -10,6 +10,31 @@ namespace acp {
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanWaves = kPlanThreads / 64;
 
+// Values of a thread's run that the per-head scans keep in registers, and the batch
+// in which a longer run is read.
+constexpr int kRunHeld = 16;
+// A thread's run in a head of n positions: as even as a multiple of 4 allows, so that
+// every run is whole float4s (n itself being a multiple of 4).
+__device__ __forceinline__ int run_length(int n) { return (n + 4 * kPlanThreads - 1) / (4 * kPlanThreads) * 4; }
+
+// x[i .. i + kRunHeld) of a run of n values into v, zeros past its end; all loads are
+// requested before any is waited for.  `vec`: n and i are multiples of 4 and x is
+// 16-byte aligned.
+__device__ __forceinline__ void load_run(const float* __restrict__ x, int i, int n, bool vec,
+                                         float (&v)[kRunHeld]) {
+    if (vec) {
+#pragma unroll
+        for (int k = 0; k < kRunHeld; k += 4) {
+            float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (i + k < n) q = *reinterpret_cast<const float4*>(x + i + k);
+            v[k] = q.x; v[k + 1] = q.y; v[k + 2] = q.z; v[k + 3] = q.w;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kRunHeld; ++k) v[k] = i + k < n ? x[i + k] : 0.f;
+    }
+}
+
 // Reductions over the 16 lanes of each row of a wave (DPP: swap neighbours, swap
 // pairs, mirror halves of 8, mirror the 16); every lane of the row ends with the
 // row's result.

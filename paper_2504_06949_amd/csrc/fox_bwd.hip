@@ -25,11 +25,11 @@ namespace acp {
 
 // ---------------------------------------------------------------------------
 // dlog f_l = sum_{i >= l} (rowsum_i - colsum_i), accumulated in float64.  Each
-// thread owns a contiguous run (held in registers up to kScanHeld values); one
-// round through LDS carries the waves' totals for the suffix sums.
+// thread owns a contiguous run of whole float4s (kept in registers up to kRunHeld
+// values, else read again in batches of that many, from the end); one round through
+// LDS carries the waves' totals for the suffix sums.
 // ---------------------------------------------------------------------------
-constexpr int kScanThreads = 1024;
-constexpr int kScanHeld = 16;
+constexpr int kScanThreads = kPlanThreads;
 
 __global__ __launch_bounds__(kScanThreads) void dlogf_kernel(const float* __restrict__ rowsum,
                                                              const float* __restrict__ colsum,
@@ -38,35 +38,24 @@ __global__ __launch_bounds__(kScanThreads) void dlogf_kernel(const float* __rest
     __shared__ double s_tot[kWaves];
     const int bh = blockIdx.x, t = threadIdx.x, lane = t & 63, wid = t >> 6;
     const size_t head = (size_t)bh * L;
-    const int per = (L + kScanThreads - 1) / kScanThreads;
-    const int beg = min(t * per, L), n = min(beg + per, L) - beg;
-    const bool held = per <= kScanHeld;
-    const bool vec = held && (per & 3) == 0;   // then n is per or 0: float4 accesses
-    double dv[kScanHeld];
-    if (vec) {
+    const int per = run_length(L);
+    const int beg = min(t * per, L), n = min(beg + per, L) - beg;   // multiples of 4
+    const float* rs = rowsum + head + beg;
+    const float* cs = colsum + head + beg;
+    double dv[kRunHeld];
+    auto load = [&](int b) __attribute__((always_inline)) {
+        float r[kRunHeld], c[kRunHeld];
+        load_run(rs, b, n, true, r);
+        load_run(cs, b, n, true, c);
 #pragma unroll
-        for (int i = 0; i < kScanHeld; i += 4) {
-            float4 r = make_float4(0.f, 0.f, 0.f, 0.f), c = r;
-            if (i < n) {
-                r = *reinterpret_cast<const float4*>(rowsum + head + beg + i);
-                c = *reinterpret_cast<const float4*>(colsum + head + beg + i);
-            }
-            dv[i] = (double)r.x - (double)c.x;
-            dv[i + 1] = (double)r.y - (double)c.y;
-            dv[i + 2] = (double)r.z - (double)c.z;
-            dv[i + 3] = (double)r.w - (double)c.w;
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < kScanHeld; ++i)
-            dv[i] = held && i < n ? (double)rowsum[head + beg + i] - (double)colsum[head + beg + i] : 0.0;
-    }
+        for (int i = 0; i < kRunHeld; ++i) dv[i] = (double)r[i] - (double)c[i];
+    };
     double local = 0.0;
-    if (held) {
+    const int last = n > 0 ? (n - 1) / kRunHeld * kRunHeld : 0;   // the run's last batch
+    for (int b = 0; b <= last; b += kRunHeld) {
+        load(b);
 #pragma unroll
-        for (int i = 0; i < kScanHeld; ++i) local += dv[i];
-    } else {
-        for (int i = 0; i < n; ++i) local += (double)rowsum[head + beg + i] - (double)colsum[head + beg + i];
+        for (int i = 0; i < kRunHeld; ++i) local += dv[i];
     }
     // inclusive suffix sums over the lanes of the wave: within each row of 16 by
     // zero-filled shifts toward lower lanes, then the totals of the later rows
@@ -90,30 +79,18 @@ __global__ __launch_bounds__(kScanThreads) void dlogf_kernel(const float* __rest
         after = readlane_f64(row16_reduce(v, [](double x, double y) { return x + y; }), 0);
     }
     double run = after + (suf - local);   // sum over the threads after this one
-    if (vec) {
+    for (int b = last; b >= 0; b -= kRunHeld) {
+        if (b != last) load(b);   // (the last batch is still in registers)
 #pragma unroll
-        for (int i = kScanHeld - 4; i >= 0; i -= 4) {
-            if (i < n) {
+        for (int i = kRunHeld - 4; i >= 0; i -= 4) {
+            if (b + i < n) {
                 float4 o;
                 run += dv[i + 3]; o.w = (float)run;
                 run += dv[i + 2]; o.z = (float)run;
                 run += dv[i + 1]; o.y = (float)run;
                 run += dv[i];     o.x = (float)run;
-                *reinterpret_cast<float4*>(dlog_f + head + beg + i) = o;
+                *reinterpret_cast<float4*>(dlog_f + head + beg + b + i) = o;
             }
-        }
-    } else if (held) {
-#pragma unroll
-        for (int i = kScanHeld - 1; i >= 0; --i) {
-            if (i < n) {
-                run += dv[i];
-                dlog_f[head + beg + i] = (float)run;
-            }
-        }
-    } else {
-        for (int i = n - 1; i >= 0; --i) {
-            run += (double)rowsum[head + beg + i] - (double)colsum[head + beg + i];
-            dlog_f[head + beg + i] = (float)run;
         }
     }
 }

@@ -401,13 +401,14 @@ acp_status acp_gate_project(const void* X, const void* w_f, const float* b_f, in
     a.agg = (unsigned long long*)(w + y.gate_agg);
     a.incl = (unsigned long long*)(w + y.gate_incl);
     a.stats = (acp::GateStats*)(w + y.gate_stats);
-    // the float32 copy of the weights goes where the backward keeps Delta' (free
-    // until a backward runs on this workspace)
+    // The transposed weights (2 H d_model bytes) go where the backward keeps Delta' (free
+    // until a backward runs on this workspace).  The limit is the one the interface
+    // states: room for a float32 copy by groups of 4 heads.
     const size_t wq_bytes = (size_t)((H + 3) / 4) * d_model * 16;
     if (wq_bytes > (size_t)B * H * L * 4)
         return fail(ACP_EUNSUPPORTED, "d_model=%d too large for these shapes (%zu bytes of "
                     "float32 weights, %zu available)", d_model, wq_bytes, (size_t)B * H * L * 4);
-    a.wq = w + y.dsum;
+    a.wt = w + y.dsum;
     return hip_status(acp::launch_gate(a, (hipStream_t)stream), "acp_gate_project launch");
 }
 

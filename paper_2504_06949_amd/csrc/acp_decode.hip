@@ -232,8 +232,7 @@ __device__ __forceinline__ void decode_copy_rows(
 // rows (nothing orders them against each other).  The scans, one workgroup per head
 // and bound by latency, run beside the copy, which the memory bounds: as two
 // launches 8 + 32 us for 96 heads of 4096 tokens, 145 + 567 for 65536 (the scan then
-// read value by value); as one 33 and
-// 607 (event timing; two launches 39 and 711).
+// read value by value); as one 33 and 607 (event timing; two launches 39 and 711).
 template <typename T, int D>
 __global__ __launch_bounds__(kPlanThreads) void decode_init_kernel(
     const T* __restrict__ K, const T* __restrict__ V, const float* __restrict__ log_f,

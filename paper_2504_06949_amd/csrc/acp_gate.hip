@@ -3,13 +3,12 @@
 // FlashAttention form of Forgetting Attention needs c = cumsum(log f); Sec. 3,
 // "Two-stage implementation": stage 1 then only has to read c).
 //
-// gate_kernel: one workgroup per (sequence b, 64-token block), one wave per
-// group of 4 heads (several groups per wave when H > 16).
-//   * Gate logits a = w_f^T x + b_f: each lane owns one token and sums its
-//     heads' dot products in float32 in ascending feature order (a product of
-//     two bfloat16 values is exact in float32, so every step rounds once), the
-//     bias added last.  Token rows and weights (a float32 copy made by the
-//     set-up kernel) stream through LDS.  log f = -softplus(-a) in float64, rounded once.
+// gate_kernel: one workgroup per (sequence b, 64-token block).
+//   * Gate logits a = w_f^T x + b_f: every (token, head) sums its products in
+//     float32 in ascending feature order (a product of two bfloat16 values is exact
+//     in float32, so every step rounds once), the bias added last.  Token rows and
+//     weights (transposed by the set-up kernel) stream through LDS.
+//     log f = -softplus(-a) in float64, rounded once.
 //   * c: a scan of the block's 64 gates per head (float64 while they span under
 //     53 bits, else double-double), then a double-double chained scan across
 //     the blocks of the sequence (decoupled look-back): each wave
@@ -43,35 +42,20 @@ namespace acp {
 constexpr unsigned long long kUnpublished = 0x7FF4ACB0DEAD0001ull;   // a signalling NaN
 constexpr int kGateSpinLimit = 1 << 22;
 
-__device__ __forceinline__ float bf16_bits_to_f32(unsigned short b) {
-    return __uint_as_float((unsigned)b << 16);
-}
-
-// Set-up before every call: descriptor words unpublished, and the weights as float32 in [group of 4 heads][feature][4] order (heads past H
-// zero), so that the producer reads a group's four weights of a feature as one
-// uniform 16-byte load.
+// Set-up before every call: descriptor words unpublished, and the weights transposed
+// to [head][feature], so that the producer's loads of a tile are whole 16-byte pieces.
 __global__ __launch_bounds__(256) void gate_init_kernel(unsigned long long* __restrict__ agg,
                                                         unsigned long long* __restrict__ incl,
                                                         int nwords,
                                                         const unsigned short* __restrict__ W,
-                                                        float4* __restrict__ wq, int Dm, int H,
-                                                        int nquad) {
+                                                        unsigned short* __restrict__ wt, int Dm,
+                                                        int H) {
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < nquad * Dm) {
-        const int quad = i / Dm, k = i % Dm, h0 = 4 * quad;
-        const unsigned short* wr = W + (size_t)k * H + h0;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        v.x = bf16_bits_to_f32(wr[0]);
-        if (h0 + 1 < H) v.y = bf16_bits_to_f32(wr[1]);
-        if (h0 + 2 < H) v.z = bf16_bits_to_f32(wr[2]);
-        if (h0 + 3 < H) v.w = bf16_bits_to_f32(wr[3]);
-        wq[i] = v;
-    }
+    if (i < H * Dm) wt[(size_t)(i % H) * Dm + i / H] = W[i];
     if (i < nwords) {
         agg[i] = kUnpublished;
         incl[i] = kUnpublished;
     }
-
 }
 
 __device__ __forceinline__ void publish(unsigned long long* w, DD v) {
@@ -87,26 +71,57 @@ __device__ __forceinline__ double bits_f64(unsigned long long b) {
     return __longlong_as_double((long long)b);
 }
 
-// A workgroup of 4 waves takes one (sequence b, 64-token block) for every head:
-// wave w computes the groups of 4 heads w, w + 4, ...  The block's token rows
-// and the groups' weights stream through LDS 64 features at a time
-// (double-buffered, each tile loaded once, coalesced, by the whole workgroup);
-// each lane reads its token's features from its LDS row.  The tile's next
-// global loads are held in named registers (an indexed array of them was
-// placed in scratch memory, whose stores waited for the loads).
+// A workgroup of 4 waves takes one (sequence b, 64-token block) for every head; wave
+// w forms the logits of tokens 16 w .. + 15.  The block's token rows and the weights
+// stream through LDS 64 features at a time (double-buffered, each tile loaded once,
+// coalesced, by the whole workgroup, two tiles ahead in named registers: an indexed
+// array of them was placed in scratch memory).
+//
+// The logits' reduction order is fixed (ascending features, every step rounded once),
+// so each (token, head) is one chain of d_model dependent multiply-adds, and the kernel
+// is bound by how few instructions and cycles a feature takes:
+//   * up to 16 heads, on the VALU: lane l takes token 16 w + l / 4 and the N heads
+//     l % 4 + 4 q, with the weights as float32 in LDS: one conversion and N multiply-adds
+//     per feature, all operands per lane (no broadcast).
+//   * more heads, on the matrix cores, one feature at a time:
+//     v_mfma_f32_4x4x1_16b_f32, whose 16 independent 4 x 4 blocks are one rounded
+//     multiply-add per element (checked against fmaf bit for bit over cancelling,
+//     subnormal and mixed magnitudes).  Block 4 i + j takes tokens 4 i .. + 3 of the wave
+//     and heads 4 j .. + 3 of a group of 16: lane l holds the features of token
+//     4 (l / 16) + l % 4 and the weights of head l % 16, and ends with the logits of tokens
+//     4 (l / 16) + (0..3), head l % 16.  A dependent one takes about 44 cycles, whatever the
+//     number of heads, which is why fewer go to the VALU.
+//
+// Measured with the set-up kernel (event timing, us) against the earlier form (a lane per
+// token and 4 heads per wave, weights broadcast from LDS, one look-back after the other):
+// 32768 tokens of d_model 768: 4 heads 33.7 -> 24.0, 8 38.6 -> 29.3, 12 41.9 -> 36.0, 16
+// 44.4 -> 41.8, 20 63.6 -> 59.0; 1088 tokens of 1088, 24 heads 62.2 -> 54.0.  12 heads on
+// the matrix cores: 38.5.  X alone is 50 MB, 10 us at the copy rate; 20 of the 36 us are the
+// two launches, log f and the look-back (measured at d_model 64).
 constexpr int kGateThreads = 256;
 constexpr int kGateTile = 64;          // features per tile (d_model % 64 == 0)
-constexpr int kGateRow = 72;           // bf16 per LDS row (rows padded to 144 bytes)
-constexpr int kGateMaxQuad = 16;       // H <= 64
+constexpr int kGateRow = 72;           // bf16 per LDS row (144 bytes: 16 rows cover all banks)
+constexpr int kGateWRow = 68;          // floats per LDS row of VALU weights (272 bytes: 4 rows
+                                       // in 4 different bank groups)
+constexpr int kGateLogitRow = 68;      // floats per head of the staged logits
 
+// the exact float32 of the low / high bfloat16 of a word
+__device__ __forceinline__ float bf16_lo(unsigned x) { return __uint_as_float(x << 16); }
+__device__ __forceinline__ float bf16_hi(unsigned x) { return __uint_as_float(x & 0xffff0000u); }
+
+// N: heads per lane (VALU), or groups of 16 heads (kMfma)
+template <int N, bool kMfma>
 __global__ __launch_bounds__(kGateThreads) void gate_kernel(
-    const __bf16* __restrict__ X, const float4* __restrict__ wq,
-    const float* __restrict__ bias, int L, int Dm, int H, int nblk, int nquad,
+    const __bf16* __restrict__ X, const __bf16* __restrict__ wt_g,
+    const float* __restrict__ bias, int L, int Dm, int H, int nblk,
     float* __restrict__ log_f, float* __restrict__ c, unsigned long long* __restrict__ agg,
     unsigned long long* __restrict__ incl, GateStats* __restrict__ st) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char gsm[];
-    __bf16* xt = reinterpret_cast<__bf16*>(gsm);                           // [2][64][kGateRow]
-    float4* wt = reinterpret_cast<float4*>(gsm + 2 * 64 * kGateRow * 2);  // [2][nquad][64]
+    constexpr int kWRows = (kMfma ? 16 : 4) * N;           // weight rows of a tile (heads past H zero)
+    constexpr int kWPer = (kWRows * 8 + kGateThreads - 1) / kGateThreads;   // 16-byte pieces per thread
+    constexpr int kXBytes = 64 * kGateRow * 2;
+    constexpr int kWBytes = kWRows * (kMfma ? kGateRow * 2 : kGateWRow * 4);
+    __shared__ __attribute__((aligned(16))) unsigned char gsm[2 * (kXBytes + kWBytes)];
+    static_assert(sizeof(gsm) >= kWRows * kGateLogitRow * sizeof(float), "staged logits");
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int blk = blockIdx.x % nblk, b = blockIdx.x / nblk;
@@ -114,112 +129,144 @@ __global__ __launch_bounds__(kGateThreads) void gate_kernel(
     const int ntile = Dm / kGateTile;
     const __bf16* xsrc = X + ((size_t)b * L + 64 * blk) * Dm;   // the block's 64 rows
 
-    // tile t: 512 pieces of 16 bytes of X (row p / 8, part p % 8) and nquad * 64
-    // float4 of weights; thread tid takes pieces tid, tid + 256, ...
-    const int nw4 = nquad * kGateTile;
-    uint4 xr0, xr1;
-    float4 wr0, wr1, wr2, wr3;
-    auto fetch = [&](int t) __attribute__((always_inline)) {
-        const int p0 = tid, p1 = tid + kGateThreads;
-        xr0 = *reinterpret_cast<const uint4*>(xsrc + (size_t)(p0 >> 3) * Dm + kGateTile * t + 8 * (p0 & 7));
-        xr1 = *reinterpret_cast<const uint4*>(xsrc + (size_t)(p1 >> 3) * Dm + kGateTile * t + 8 * (p1 & 7));
-        auto wload = [&](int p) __attribute__((always_inline)) {
-            return p < nw4 ? wq[(size_t)(p / kGateTile) * Dm + kGateTile * t + p % kGateTile]
-                           : make_float4(0.f, 0.f, 0.f, 0.f);
-        };
-        wr0 = wload(tid);
-        wr1 = wload(tid + kGateThreads);
-        wr2 = wload(tid + 2 * kGateThreads);
-        wr3 = wload(tid + 3 * kGateThreads);
+    // Tile t: 512 pieces of 16 bytes of X (row p / 8, part p % 8) and 8 H of the weights;
+    // thread tid takes pieces tid, tid + 256, ...
+    struct Pieces {
+        uint4 x0, x1, w0, w1;
     };
-    auto stash = [&](int buf) __attribute__((always_inline)) {
-        const int p0 = tid, p1 = tid + kGateThreads;
-        *reinterpret_cast<uint4*>(xt + (buf * 64 + (p0 >> 3)) * kGateRow + 8 * (p0 & 7)) = xr0;
-        *reinterpret_cast<uint4*>(xt + (buf * 64 + (p1 >> 3)) * kGateRow + 8 * (p1 & 7)) = xr1;
-        if (tid < nw4) wt[buf * nw4 + tid] = wr0;
-        if (tid + kGateThreads < nw4) wt[buf * nw4 + tid + kGateThreads] = wr1;
-        if (tid + 2 * kGateThreads < nw4) wt[buf * nw4 + tid + 2 * kGateThreads] = wr2;
-        if (tid + 3 * kGateThreads < nw4) wt[buf * nw4 + tid + 3 * kGateThreads] = wr3;
+    auto fetch = [&](int t) __attribute__((always_inline)) {
+        Pieces r;
+        const int row = tid >> 3, part = 8 * (tid & 7) + kGateTile * t;
+        r.x0 = *reinterpret_cast<const uint4*>(xsrc + (size_t)row * Dm + part);
+        r.x1 = *reinterpret_cast<const uint4*>(xsrc + (size_t)(row + 32) * Dm + part);
+        r.w0 = make_uint4(0u, 0u, 0u, 0u);
+        r.w1 = r.w0;
+        if (row < H) r.w0 = *reinterpret_cast<const uint4*>(wt_g + (size_t)row * Dm + part);
+        if (kWPer > 1 && row + 32 < H)
+            r.w1 = *reinterpret_cast<const uint4*>(wt_g + (size_t)(row + 32) * Dm + part);
+        return r;
+    };
+    auto stash = [&](const Pieces& r, int buf) __attribute__((always_inline)) {
+        const int row = tid >> 3, part = 16 * (tid & 7);
+        unsigned char* xb = gsm + buf * kXBytes;
+        unsigned char* wb = gsm + 2 * kXBytes + buf * kWBytes;
+        *reinterpret_cast<uint4*>(xb + row * kGateRow * 2 + part) = r.x0;
+        *reinterpret_cast<uint4*>(xb + (row + 32) * kGateRow * 2 + part) = r.x1;
+        if constexpr (kMfma) {
+            if (row < kWRows) *reinterpret_cast<uint4*>(wb + row * kGateRow * 2 + part) = r.w0;
+            if (kWPer > 1 && row + 32 < kWRows)
+                *reinterpret_cast<uint4*>(wb + (row + 32) * kGateRow * 2 + part) = r.w1;
+        } else if (row < kWRows) {
+            float* f = reinterpret_cast<float*>(wb) + row * kGateWRow + 8 * (tid & 7);
+            *reinterpret_cast<float4*>(f) = make_float4(bf16_lo(r.w0.x), bf16_hi(r.w0.x), bf16_lo(r.w0.y), bf16_hi(r.w0.y));
+            *reinterpret_cast<float4*>(f + 4) = make_float4(bf16_lo(r.w0.z), bf16_hi(r.w0.z), bf16_lo(r.w0.w), bf16_hi(r.w0.w));
+        }
     };
 
     // ---- logits: float32, ascending feature order -----------------------------
-    float acc[4][4];
+    f32x4 acc[N];   // (VALU: element 0 alone)
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int g = 0; g < N; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the lane's token of the wave's 16 and its head of 16 (of 4 on the VALU)
+    const int ltok = kMfma ? 4 * (lane >> 4) + (lane & 3) : lane >> 2;
+    const int lhead = kMfma ? lane & 15 : lane & 3;
+    auto products = [&](int buf) __attribute__((always_inline)) {
+        const unsigned char* xrow = gsm + buf * kXBytes + (16 * w + ltok) * kGateRow * 2;
+        const unsigned char* wb = gsm + 2 * kXBytes + buf * kWBytes;
+        if constexpr (kMfma) {
+            const unsigned char* wrow = wb + lhead * kGateRow * 2;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[r][j] = 0.f;
-    fetch(0);
-    stash(0);
-    __syncthreads();
-    // Each group's 64 features of a tile are taken in steps of 8, the LDS reads
-    // of step g + 1 (the lane's 8 features, the group's 8 weight vectors) issued
-    // before the 32 FMAs of step g, so that their latency is covered.
-    for (int t = 0; t < ntile; ++t) {
-        const int buf = t & 1;
-        if (t + 1 < ntile) fetch(t + 1);
-        const __bf16* xrow = xt + (buf * 64 + lane) * kGateRow;
+            for (int k = 0; k < kGateTile / 8; ++k) {
+                const uint4 xv = *reinterpret_cast<const uint4*>(xrow + 16 * k);
+                const unsigned xw[4] = {xv.x, xv.y, xv.z, xv.w};
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int q = w + 4 * r;
-            if (q >= nquad) break;
-            const float4* wq_t = wt + buf * nw4 + q * kGateTile;
-            bf16x8 xa = *reinterpret_cast<const bf16x8*>(xrow);
-            float4 wa[8];
+                for (int g = 0; g < N; ++g) {
+                    const uint4 wv = *reinterpret_cast<const uint4*>(wrow + 16 * g * kGateRow * 2 + 16 * k);
+                    const unsigned ww[4] = {wv.x, wv.y, wv.z, wv.w};
 #pragma unroll
-            for (int e = 0; e < 8; ++e) wa[e] = wq_t[e];
-#pragma unroll
-            for (int g = 0; g < kGateTile / 8; ++g) {
-                bf16x8 xb;
-                float4 wb[8];
-                if (g + 1 < kGateTile / 8) {
-                    xb = *reinterpret_cast<const bf16x8*>(xrow + 8 * (g + 1));
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) wb[e] = wq_t[8 * (g + 1) + e];
+                    for (int e = 0; e < 4; ++e) {
+                        acc[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(bf16_lo(xw[e]), bf16_lo(ww[e]), acc[g], 0, 0, 0);
+                        acc[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(bf16_hi(xw[e]), bf16_hi(ww[e]), acc[g], 0, 0, 0);
+                    }
                 }
-                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+            // (two steps of 8 features at a time: with the whole tile unrolled the reads of
+            // 3 or 4 heads per lane took every register, and 48.7 us instead of 35.8)
+            const float* wrow = reinterpret_cast<const float*>(wb) + lhead * kGateWRow;
+#pragma unroll 2
+            for (int k = 0; k < kGateTile / 8; ++k) {
+                const uint4 xv = *reinterpret_cast<const uint4*>(xrow + 16 * k);
+                const unsigned xw[4] = {xv.x, xv.y, xv.z, xv.w};
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float xe = (float)xa[e];
-                    acc[r][0] = __builtin_fmaf(xe, wa[e].x, acc[r][0]);
-                    acc[r][1] = __builtin_fmaf(xe, wa[e].y, acc[r][1]);
-                    acc[r][2] = __builtin_fmaf(xe, wa[e].z, acc[r][2]);
-                    acc[r][3] = __builtin_fmaf(xe, wa[e].w, acc[r][3]);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                if (g + 1 < kGateTile / 8) {
-                    xa = xb;
+                for (int hf = 0; hf < 2; ++hf) {
+                    float4 wv[N];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) wa[e] = wb[e];
+                    for (int g = 0; g < N; ++g)
+                        wv[g] = *reinterpret_cast<const float4*>(wrow + 4 * g * kGateWRow + 8 * k + 4 * hf);
+                    const float x0 = bf16_lo(xw[2 * hf]), x1 = bf16_hi(xw[2 * hf]),
+                                x2 = bf16_lo(xw[2 * hf + 1]), x3 = bf16_hi(xw[2 * hf + 1]);
+#pragma unroll
+                    for (int g = 0; g < N; ++g) {
+                        float a = acc[g][0];
+                        a = __builtin_fmaf(x0, wv[g].x, a);
+                        a = __builtin_fmaf(x1, wv[g].y, a);
+                        a = __builtin_fmaf(x2, wv[g].z, a);
+                        acc[g][0] = __builtin_fmaf(x3, wv[g].w, a);
+                    }
                 }
             }
         }
-        if (t + 1 < ntile) stash(buf ^ 1);
-        __syncthreads();
+    };
+    Pieces pa = fetch(0), pb = pa;
+    stash(pa, 0);
+    if (ntile > 1) pa = fetch(1);
+    __syncthreads();
+    // tile t in LDS, tile t + 1 in registers, tile t + 2 requested
+    for (int t = 0; t < ntile; t += 2) {
+        if (t + 2 < ntile) pb = fetch(t + 2);
+        products(0);
+        if (t + 1 < ntile) stash(pa, 1);
+        lds_barrier();
+        if (t + 1 >= ntile) break;
+        if (t + 3 < ntile) pa = fetch(t + 3);
+        products(1);
+        if (t + 2 < ntile) stash(pb, 0);
+        lds_barrier();
     }
-
-    // ---- per group of heads: log f, statistics, the block scan, the chained
-    // prefix, c ---------------------------------------------------------------------
-#pragma unroll 1
-    for (int r = 0; r < 4; ++r) {
-        const int q = w + 4 * r;
-        if (q >= nquad) break;
-        const int h0 = 4 * q, nh = min(4, H - h0);
-        float a4[4];   // this group's logits (selected, not indexed, from acc)
+    // the logits to [head][token], over the tiles (the last barrier ended their reads)
+    float* lg = reinterpret_cast<float*>(gsm);
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            a4[j] = r == 0 ? acc[0][j] : r == 1 ? acc[1][j] : r == 2 ? acc[2][j] : acc[3][j];
-        DD excl_mine{0.0, 0.0};   // lane j < nh: exclusive prefix of head h0 + j
-        DD abs_mine{0.0, 0.0};    // lane j < nh: the block's statistics of head h0 + j
+    for (int g = 0; g < N; ++g) {
+        if constexpr (kMfma)
+            *reinterpret_cast<f32x4*>(lg + (16 * g + lhead) * kGateLogitRow + 16 * w + 4 * (lane >> 4)) = acc[g];
+        else
+            lg[(4 * g + lhead) * kGateLogitRow + 16 * w + ltok] = acc[g][0];
+    }
+    lds_barrier();
+
+    // ---- per head: log f, statistics, the block scan, the chained prefix, c.  Wave w
+    // takes heads w, w + 4, ..., up to four at a time: lane = token of the block, and
+    // lane j keeps the results of the round's head j ----------------------------------
+#pragma unroll 1
+    for (int r = w; r < H; r += 16) {
+        auto head = [&](int j) { return r + 4 * j; };
+        const int nh = min(4, (H - r + 3) / 4);
+        float a4[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a4[j] = j < nh ? lg[head(j) * kGateLogitRow + lane] : 0.f;
+        DD excl_mine{0.0, 0.0};   // lane j < nh: exclusive prefix of head j
+        DD abs_mine{0.0, 0.0};    // lane j < nh: the block's statistics of head j
         int lsb_mine = 1 << 30, flags_mine = 0;
         DD scan[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             scan[j] = DD{0.0, 0.0};
             if (j >= nh) continue;
-            const double a = (double)(a4[j] + bias[h0 + j]);
+            const double a = (double)(a4[j] + bias[head(j)]);
             const double sp = fmax(-a, 0.0) + log1p(exp(-fabs(a)));   // softplus(-a)
             const float lf32 = (float)(-sp);
-            const size_t bh = (size_t)b * H + h0 + j;
+            const size_t bh = (size_t)b * H + head(j);
             log_f[bh * L + tok] = lf32;
             // statistics for stage 1's checks, and the block's scan: in float64
             // while the block's own 64 gates span under 53 bits (then every float64
@@ -227,13 +274,12 @@ __global__ __launch_bounds__(kGateThreads) void gate_kernel(
             const bool bad = !__builtin_isfinite(lf32);
             const double gv = bad ? 0.0 : (double)lf32;
             const int lsb = bad || lf32 == 0.f ? (1 << 30) : lsb_exp(lf32);
-            double sabs_f = __builtin_fabs(gv);
-            int slsb = lsb;
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                sabs_f += __shfl_xor(sabs_f, off);
-                slsb = min(slsb, __shfl_xor(slsb, off));
-            }
+            const double ra = row16_reduce(__builtin_fabs(gv), [](double x, double y) { return x + y; });
+            const double sabs_f = ((readlane_f64(ra, 0) + readlane_f64(ra, 16)) + readlane_f64(ra, 32)) +
+                                  readlane_f64(ra, 48);
+            const int rl = row16_reduce(lsb, [](int x, int y) { return min(x, y); });
+            const int slsb = min(min(__builtin_amdgcn_readlane(rl, 0), __builtin_amdgcn_readlane(rl, 16)),
+                                 min(__builtin_amdgcn_readlane(rl, 32), __builtin_amdgcn_readlane(rl, 48)));
             const int biased = (int)((__double_as_longlong(sabs_f) >> 52) & 0x7ff);
             const bool bwide = __builtin_amdgcn_readfirstlane(
                 sabs_f > 0.0 && (biased > 0 ? biased : 1) - 1023 + 1 - slsb >= 53);
@@ -251,7 +297,7 @@ __global__ __launch_bounds__(kGateThreads) void gate_kernel(
                 flags_mine = anybad ? 2 : 0;
             }
         }
-        // block totals (lane j holds head h0 + j's), published before the look-back
+        // block totals (lane j holds head j's), published before the look-back
         DD total{0.0, 0.0};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -259,63 +305,84 @@ __global__ __launch_bounds__(kGateThreads) void gate_kernel(
             if (lane == j) total = tj;
         }
         if (lane < nh) {
-            const size_t d = ((size_t)b * H + h0 + lane) * nblk + blk;
+            const size_t d = ((size_t)b * H + head(lane)) * nblk + blk;
             publish((blk == 0 ? incl : agg) + 2 * d, total);
         }
-        // Look-back, one head at a time with the whole wave: lane l reads block
-        // i0 - l's descriptors, 64 blocks per round.  The nearest block with its
-        // inclusive prefix published ends the walk if every block after it has
-        // its total published; otherwise the round is read again.  A round with
-        // no prefix but all 64 totals adds them and moves 64 blocks back.
-        for (int j = 0; j < nh; ++j) {
-            if (blk == 0) break;
-            const size_t d0 = ((size_t)b * H + h0 + j) * nblk;
-            DD run{0.0, 0.0};
-            int i0 = blk - 1, spins = 0;
-            bool timed_out = false;
-            while (i0 >= 0) {
-                const int i = i0 - lane;
-                unsigned long long p = kUnpublished, pl = kUnpublished;
-                unsigned long long qq = kUnpublished, ql = kUnpublished;
-                if (i >= 0) {
-                    const size_t w2 = 2 * (d0 + i);
-                    p = peek(&incl[w2]);
-                    pl = peek(&incl[w2 + 1]);
-                    qq = peek(&agg[w2]);
-                    ql = peek(&agg[w2 + 1]);
+        // Look-back, the whole wave on every head of the round, whose descriptors are
+        // requested together (one head after the other, each round trip to memory came
+        // on top of the last): lane l reads block i0 - l's, 64 blocks per round.  The
+        // nearest block with its inclusive prefix published ends a head's walk if every
+        // block after it has its total published; otherwise the round is read again.  A
+        // round with no prefix but all 64 totals adds them and moves 64 blocks back.
+        DD run[4];
+        int i0[4];
+        unsigned open = blk == 0 ? 0u : (1u << nh) - 1u;   // heads still walking (uniform)
+        int spins = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            run[j] = DD{0.0, 0.0};
+            i0[j] = blk - 1;
+        }
+        while (open != 0u) {
+            unsigned long long p[4], pl[4], qq[4], ql[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                p[j] = pl[j] = qq[j] = ql[j] = kUnpublished;
+                const int i = i0[j] - lane;
+                if ((open >> j & 1u) && i >= 0) {
+                    const size_t w2 = 2 * (((size_t)b * H + head(j)) * nblk + i);
+                    p[j] = peek(&incl[w2]);
+                    pl[j] = peek(&incl[w2 + 1]);
+                    qq[j] = peek(&agg[w2]);
+                    ql[j] = peek(&agg[w2 + 1]);
                 }
+            }
+            bool moved = false;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (!(open >> j & 1u)) continue;
+                const int i = i0[j] - lane;
                 // lanes whose block lies before the sequence count as published zeros
-                const bool has_p = i >= 0 && p != kUnpublished && pl != kUnpublished;
-                const bool has_q = i < 0 || (qq != kUnpublished && ql != kUnpublished) || has_p;
+                const bool has_p = i >= 0 && p[j] != kUnpublished && pl[j] != kUnpublished;
+                const bool has_q = i < 0 || (qq[j] != kUnpublished && ql[j] != kUnpublished) || has_p;
                 const unsigned long long pm = __ballot(has_p);
                 const int stop = pm ? __builtin_ctzll(pm) : 64;      // nearest prefix
                 const unsigned long long need = stop == 64 ? ~0ull : ((1ull << stop) - 1ull);
                 const unsigned long long qm = __ballot(has_q);
-                if ((qm & need) == need) {
-                    if (stop == 0) {   // the previous block's prefix alone: no reduction
-                        run = dd_add(run, DD{readlane_f64(bits_f64(p), 0), readlane_f64(bits_f64(pl), 0)});
-                        break;
-                    }
+                if ((qm & need) != need) continue;
+                moved = true;
+                if (stop == 0) {   // the previous block's prefix alone: no reduction
+                    run[j] = dd_add(run[j], DD{readlane_f64(bits_f64(p[j]), 0), readlane_f64(bits_f64(pl[j]), 0)});
+                } else {
                     DD v{0.0, 0.0};
-                    if (lane < stop && i >= 0) v = DD{bits_f64(qq), bits_f64(ql)};
-                    if (lane == stop) v = DD{bits_f64(p), bits_f64(pl)};
+                    if (lane < stop && i >= 0) v = DD{bits_f64(qq[j]), bits_f64(ql[j])};
+                    if (lane == stop) v = DD{bits_f64(p[j]), bits_f64(pl[j])};
                     double sum;
-                    run = dd_add(run, wave_sum_f64_if_exact(v, sum) ? DD{sum, 0.0} : wave_sum_dd(v));
-                    if (stop < 64) break;
-                    i0 -= 64;
-                    spins = 0;
-                    continue;
+                    run[j] = dd_add(run[j], wave_sum_f64_if_exact(v, sum) ? DD{sum, 0.0} : wave_sum_dd(v));
                 }
-                if (++spins > kGateSpinLimit) {
-                    timed_out = true;
-                    break;
+                i0[j] -= 64;
+                if (stop < 64 || i0[j] < 0) {
+                    open &= ~(1u << j);
+                    if (lane == j) {
+                        excl_mine = run[j];
+                        publish(&incl[2 * (((size_t)b * H + head(j)) * nblk + blk)], dd_add(run[j], total));
+                    }
                 }
-                __builtin_amdgcn_s_sleep(1);
             }
-            if (lane == j) {
-                excl_mine = run;
-                if (timed_out) flags_mine |= 32;
-                publish(&incl[2 * (d0 + blk)], dd_add(run, total));
+            if (moved) {
+                spins = 0;
+            } else if (++spins > kGateSpinLimit) {
+                // time-out: the heads still open go on with what they have
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if ((open >> j & 1u) && lane == j) {
+                        excl_mine = run[j];
+                        flags_mine |= 32;
+                        publish(&incl[2 * (((size_t)b * H + head(j)) * nblk + blk)], dd_add(run[j], total));
+                    }
+                open = 0u;
+            } else {
+                __builtin_amdgcn_s_sleep(1);
             }
         }
         if (lane < nh) {
@@ -324,32 +391,41 @@ __global__ __launch_bounds__(kGateThreads) void gate_kernel(
             g.abs_lo = abs_mine.lo;
             g.min_lsb = lsb_mine;
             g.flags = flags_mine;
-            st[((size_t)b * H + h0 + lane) * nblk + blk] = g;
+            st[((size_t)b * H + head(lane)) * nblk + blk] = g;
         }
         // c of the block: exclusive prefix + the in-block inclusive scan
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if (j >= nh) continue;
             const DD ex = readlane_dd(excl_mine, j);
-            c[((size_t)b * H + h0 + j) * L + tok] = dd_to_f32(dd_add(ex, scan[j]));
+            c[((size_t)b * H + head(j)) * L + tok] = dd_to_f32(dd_add(ex, scan[j]));
         }
     }
 }
 
+template <int N, bool kMfma>
+static void gate_t(const GateArgs& a, hipStream_t s) {
+    const int nblk = a.L / 64;
+    hipLaunchKernelGGL((gate_kernel<N, kMfma>), dim3(a.B * nblk), dim3(kGateThreads), 0, s,
+                       (const __bf16*)a.X, (const __bf16*)a.wt, a.bias, a.L, a.Dm, a.H, nblk,
+                       a.log_f, a.c, a.agg, a.incl, a.stats);
+}
+
 hipError_t launch_gate(const GateArgs& a, hipStream_t s) {
-    const int nblk = a.L / 64, nquad = (a.H + 3) / 4;
-    const int ndesc = a.B * a.H * nblk;
+    const int ndesc = a.B * a.H * (a.L / 64);
     trace_begin(ACP_K_GATE, s);
-    const int ninit = max(2 * ndesc, nquad * a.Dm);
+    const int ninit = max(2 * ndesc, a.H * a.Dm);
     hipLaunchKernelGGL(gate_init_kernel, dim3((ninit + 255) / 256), dim3(256), 0, s,
                        a.agg, a.incl, 2 * ndesc, (const unsigned short*)a.W,
-                       (float4*)a.wq, a.Dm, a.H, nquad);
+                       (unsigned short*)a.wt, a.Dm, a.H);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const size_t lds = (size_t)2 * 64 * kGateRow * 2 + (size_t)2 * nquad * kGateTile * 16;
-    hipLaunchKernelGGL(gate_kernel, dim3(a.B * nblk), dim3(kGateThreads), lds, s,
-                       (const __bf16*)a.X, (const float4*)a.wq, a.bias, a.L, a.Dm, a.H,
-                       nblk, nquad, a.log_f, a.c, a.agg, a.incl, a.stats);
+    if (a.H <= 4) gate_t<1, false>(a, s);
+    else if (a.H <= 8) gate_t<2, false>(a, s);
+    else if (a.H <= 12) gate_t<3, false>(a, s);
+    else if (a.H <= 16) gate_t<4, false>(a, s);
+    else if (a.H <= 32) gate_t<2, true>(a, s);
+    else gate_t<4, true>(a, s);
     e = hipGetLastError();
     trace_end(ACP_K_GATE, s);
     return e;

@@ -51,7 +51,7 @@ struct GateArgs {
     unsigned long long* agg;  // [B*H, L/64, 2] block totals (float64 bits of hi, lo)
     unsigned long long* incl; // [B*H, L/64, 2] inclusive prefixes (float64 bits of hi, lo)
     GateStats* stats;         // [B*H, L/64]
-    void* wq;                 // [ceil(H/4), Dm] float4: the weights by group of 4 heads
+    void* wt;                 // [H, Dm] bf16: the weights transposed
 };
 
 struct FwdArgs {

@@ -336,10 +336,16 @@ static acp_status fwd_common(const void* Q, const void* K, const void* V, const 
     if (gated) p.gate = (const acp::GateStats*)(w + y.gate_stats);
     hipError_t e = acp::launch_plan(p, (hipStream_t)stream);
     if (e != hipSuccess) return hip_status(e, "fox_attn_fwd boundary launch");
-    if (dt == ACP_BF16) {
-        e = acp::launch_schedule((const long long*)(w + y.kept), (const int*)(w + y.rs),
-                                 (const int*)(w + y.ce), B * H, L / 64, (L + 127) / 128,
-                                 (int*)(w + y.sched_q), (int*)(w + y.sched_k), (hipStream_t)stream);
+    acp::ScheduleArgs sched{};
+    sched.kept = (const long long*)(w + y.kept);
+    sched.row_start = (const int*)(w + y.rs);
+    sched.col_end = (const int*)(w + y.ce);
+    sched.BH = B * H; sched.M = L / 64; sched.nb = (L + 127) / 128;
+    sched.sched_q = (int*)(w + y.sched_q);
+    sched.sched_k = (int*)(w + y.sched_k);
+    const bool direct = acp::forward_direct(d, B * H * sched.nb, sched.nb);
+    if (dt == ACP_BF16 && !direct) {
+        e = acp::launch_schedule(sched, (hipStream_t)stream);
         if (e != hipSuccess) return hip_status(e, "fox_attn_fwd schedule launch");
     }
     acp::FwdArgs f{};
@@ -348,7 +354,8 @@ static acp_status fwd_common(const void* Q, const void* K, const void* V, const 
     f.c = (const float*)(w + y.c);
     f.row_start = (const int*)(w + y.rs);
     f.u = (const double*)(w + y.u);
-    f.sched = (const int*)(w + y.sched_q);
+    f.sched = sched;
+    f.direct = direct;
     f.O = O;
     f.lse = lse;
     f.lse2 = (float*)(w + y.lse2);

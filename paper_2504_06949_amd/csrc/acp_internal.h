@@ -54,6 +54,28 @@ struct GateArgs {
     void* wt;                 // [H, Dm] bf16: the weights transposed
 };
 
+// Tables of B*H*nb entries bh * nb + block, nb = ceil(L / 128): per XCD, heads placed by
+// kept count when there are few, blocks largest first.
+struct ScheduleArgs {
+    const long long* kept;    // [BH]
+    const int* row_start;     // [BH, M]
+    const int* col_end;       // [BH, M]
+    int BH, M, nb;
+    int* sched_q;             // query blocks (forward, dQ pass)
+    int* sched_k;             // key blocks (dK/dV pass)
+};
+// Blocks per head from which heads are placed in parts.
+constexpr int kLongBlocks = 32;
+// Whether the forward takes its blocks without the tables and fills them itself: as many
+// blocks as the CUs hold at once (4 per CU at d = 64, 2 at 128).  Beyond that the
+// tables' order and their keeping of a head on one XCD are worth their kernel.
+// Measured, us for the whole forward, tables first -> direct: 48 heads of 1024 tokens 43
+// -> 32, 100 of 640 37 -> 34; more blocks, forward kernel alone: 192 of 1024 (1536
+// blocks) 43 -> 47, 128 of 2048 (2048) 77 -> 92; d = 128, 32 of 3072 (768) 82 -> 92.
+inline bool forward_direct(int d, int nblocks, int nb) {
+    return nb < kLongBlocks && nblocks <= (d == 64 ? 1024 : 512);
+}
+
 struct FwdArgs {
     const void* Q;
     const void* K;
@@ -63,7 +85,8 @@ struct FwdArgs {
     const float* c;
     const int* row_start;
     const double* u;          // [B*H] logit bound U
-    const int* sched;         // [B*H*nb] query-block schedule (bh * nb + block)
+    ScheduleArgs sched;       // the tables
+    bool direct;              // the forward fills them itself
     void* O;
     float* lse;
     float* lse2;
@@ -183,11 +206,7 @@ void trace_begin(int kernel, hipStream_t s);
 void trace_end(int kernel, hipStream_t s);
 
 int norm_chunks(int L);
-// Which (head, 128-row block) each logical workgroup id of the attention kernels
-// takes: per XCD, heads placed by kept count when there are few, blocks largest
-// first.  Tables of B*H*nb entries bh * nb + block, nb = ceil(L / 128).
-hipError_t launch_schedule(const long long* kept, const int* row_start, const int* col_end,
-                           int BH, int M, int nb, int* sched_q, int* sched_k, hipStream_t s);
+hipError_t launch_schedule(const ScheduleArgs& a, hipStream_t s);
 hipError_t launch_plan(const PlanArgs& a, hipStream_t s);
 hipError_t launch_gate(const GateArgs& a, hipStream_t s);
 hipError_t launch_fwd(const FwdArgs& a, hipStream_t s);

@@ -1,0 +1,218 @@
+// Workgroup schedule of the attention kernels: which (head, 128-row block) each
+// logical workgroup id takes.
+#pragma once
+
+#include "acp_device.h"
+#include "acp_internal.h"
+
+namespace acp {
+
+// The attention kernels' workgroups each take 128 query rows (forward, dQ) or
+// 128 keys (dK/dV) of one head.  Workgroup ids are dealt round-robin to the 8
+// XCDs; xcd_logical_id turns that into a contiguous range of logical ids per XCD,
+// and this kernel fills, per XCD range, which (head, block) each logical id
+// takes, so that
+//   - a head's workgroups run on one XCD (its K and V stay in one L2), or, when
+//     there are few long heads, on as few as a balanced load allows;
+//   - with at most kHeadsMax heads they are placed by kept-block count, largest
+//     first, each on the least loaded XCD that still has room (the same number per
+//     XCD).  What is placed are whole heads when sequences are short (below 32 of the
+//     128-row blocks), else parts of a head, every s-th of its blocks
+//     (schedule_log_parts); 8 parts per head are simply dealt out, one to each XCD.
+//     (With more heads an XCD has several of them, and reading the counts first
+//     costs this kernel 3 us: 96 heads of 4096 tokens 6.4 -> 9.3, the forward 187
+//     either way.)
+//   - otherwise they stay in bh order;
+//   - inside each XCD range the workgroups run largest first (a counting sort
+//     on their kept-tile counts), so that the range ends on small ones.
+// Grid (8, 2): x = XCD, y = 0 for the query-block table, 1 for the key-block one.
+// Entry = bh * nb + block.  Equal counts keep no particular order.
+constexpr int kHeadsMax = 64;          // heads that are placed
+constexpr int kPlaceMax = 256;         // parts that are dealt
+
+
+// log2 of the parts s per head: enough that the parts make whole rounds over the
+// XCDs, 8 (then every XCD has the same share of every head) for at most 16 heads, and
+// otherwise no more than 64 parts: a head spread further costs L2 reuse.  A head's
+// kept share runs from nearly none to all, so with one or two heads per XCD the
+// heaviest XCD decides the time.  Measured, forward: 8 heads of 32768 tokens (d = 128)
+// 1956 us undivided, 1200 in 8 parts; 12 heads of 8128 tokens 198 us in bh order, 162
+// in 4 parts, 135 in 8.  (48 heads of 16384 dealt back and forth instead of to the least
+// loaded XCD: every kernel 2% slower.)  Training step at 4 x 16 heads of 8192 tokens: 1.73 ms
+// undivided, 1.77 in 2 parts, 1.83 in 4; 2 x 16 heads of 16384 (d = 128): 5.12 ms in 2
+// parts, 5.18 in 4, 5.30 in 8.
+__host__ __device__ constexpr int schedule_log_parts(int BH, int nb) {
+    if (nb < kLongBlocks) return 0;
+    int s = 0;
+    while (s < 3 && (BH <= 16 || ((BH << s) & 7) != 0 || (BH << (s + 1)) <= kHeadsMax)) ++s;
+    return BH << s <= kHeadsMax ? s : BH <= kHeadsMax / 2 ? 3 : 0;
+}
+
+struct ScheduleSmem {
+    int place[kPlaceMax];                            // part of each slot: bh * parts + part
+    int first[kPlaceMax + 1];                        // first logical id of each slot
+    __attribute__((aligned(16))) int kept[kPlaceMax];
+    int more[kPlaceMax / 64];
+    int hist[2 * kMaxBlocks + 2];                    // a block's count is at most 2M <= 4096
+    int wave[16];
+};
+
+// One of the two tables for one XCD, by a workgroup of THREADS.
+template <int THREADS>
+__device__ __forceinline__ void schedule_table(ScheduleSmem& sm, const ScheduleArgs& a, int x, int table) {
+    const int t = threadIdx.x, BH = a.BH, M = a.M, nb = a.nb;
+    const long long* kept = a.kept;
+    const int* row_start = a.row_start;
+    const int* col_end = a.col_end;
+    const int lp = schedule_log_parts(BH, nb), parts = 1 << lp, NP = BH << lp;
+    const bool deal = lp == 3 && BH <= kHeadsMax / 2;    // NP a multiple of 8, <= kPlaceMax
+    const bool greedy = !deal && NP % 8 == 0 && NP <= kHeadsMax;
+    // the head's rank by kept count (largest first, ties by index)
+    auto rank_of = [&](int bh) {
+        const int mine = sm.kept[bh];
+        int rank = 0;
+        for (int j = 0; j < BH; j += 4) {   // (padded with -1)
+            const int4 k = *reinterpret_cast<const int4*>(&sm.kept[j]);
+            rank += (k.x > mine || (k.x == mine && j < bh)) ? 1 : 0;
+            rank += (k.y > mine || (k.y == mine && j + 1 < bh)) ? 1 : 0;
+            rank += (k.z > mine || (k.z == mine && j + 2 < bh)) ? 1 : 0;
+            rank += (k.w > mine || (k.w == mine && j + 3 < bh)) ? 1 : 0;
+        }
+        return rank;
+    };
+    static_assert(THREADS >= kPlaceMax, "a thread per part");
+    if ((deal || greedy) && t < kPlaceMax) sm.kept[t] = t < BH ? (int)min(max(kept[t], 0ll), 1ll << 22) : -1;
+    __syncthreads();
+    if (deal) {
+        // slot (NP / 8) j + i: part j of the head of rank i
+        if (t < NP) sm.place[BH * (t & 7) + rank_of(t >> 3)] = t;
+    } else if (greedy && t < 64) {
+        // Wave 0 alone.  Lane j of 0-7 holds XCD j as the key load << 3 | j; each step
+        // the key that equals the minimum over the 8 lanes (the least loaded XCD with
+        // room, lowest index on ties) takes the part, and its lane writes the slot.  A
+        // head keeps at most M (M + 1) / 2 < 2^22 blocks and an XCD holds at most 8
+        // parts, so the key fits 32 bits.
+        if (t < NP) sm.first[(rank_of(t >> lp) << lp) + (t & (parts - 1))] = t;
+        // (a single wave's LDS accesses complete in order: no barrier)
+        const int hd_l = t < NP ? sm.first[t] : 0;
+        const int k_l = t < NP ? sm.kept[hd_l >> lp] << 3 : 0;
+        asm volatile("" : : "v"(hd_l), "v"(k_l));   // (waits for the LDS reads here, not in the loop)
+        const int per = NP / 8;
+        if (t < 8) {
+            unsigned key = (unsigned)t;
+            int pos = per * t;
+            const int end = pos + per;
+            for (int i = 0; i < NP; ++i) {
+                const unsigned k_i = (unsigned)__builtin_amdgcn_readlane(k_l, i);
+                const int hd_i = __builtin_amdgcn_readlane(hd_l, i);
+                // minimum over the 8 lanes: swap neighbours, pairs, quads
+                unsigned mn = min(key, (unsigned)__builtin_amdgcn_mov_dpp((int)key, 0xB1, 0xF, 0xF, false));
+                mn = min(mn, (unsigned)__builtin_amdgcn_mov_dpp((int)mn, 0x4E, 0xF, 0xF, false));
+                mn = min(mn, (unsigned)__builtin_amdgcn_mov_dpp((int)mn, 0x141, 0xF, 0xF, false));
+                const bool mine = key == mn;
+                // (the others write a spare word)
+                (mine ? &sm.place[pos] : &sm.kept[kPlaceMax - 1])[0] = hd_i;
+                pos += mine ? 1 : 0;
+                key = pos == end ? 0xffffffffu : key + (mine ? k_i : 0u);
+            }
+        }
+    }
+    if (lp > 0 && (deal || greedy)) {
+        // first logical id of slot t: part j has nb >> lp blocks, and one more below
+        // nb's remainder
+        __syncthreads();
+        const bool more = t < NP && (sm.place[t] & (parts - 1)) < (nb & (parts - 1));
+        const unsigned long long bal = __ballot(more);
+        if (t < kPlaceMax && (t & 63) == 0) sm.more[t >> 6] = __popcll(bal);
+        __syncthreads();
+        if (t < NP) {
+            int first = t * (nb >> lp) + __popcll(bal & ((1ull << (t & 63)) - 1ull));
+            for (int w = 0; w < (t >> 6); ++w) first += sm.more[w];
+            sm.first[t] = first;
+        }
+    }
+    const int nbins = 2 * M + 2;
+    for (int i = t; i < nbins; i += THREADS) sm.hist[i] = 0;
+    __syncthreads();
+
+    // this XCD's range of logical ids (as xcd_logical_id deals them)
+    const int nblocks = BH * nb, q = nblocks >> 3, r = nblocks & 7;
+    const int lo = x * q + min(x, r), hi = lo + q + (x < r ? 1 : 0);
+    int* out = table == 0 ? a.sched_q : a.sched_k;
+    // the item of a logical id in the unsorted order and its kept-tile count
+    auto item = [&](int lid, int& work) {
+        int bh, idx;
+        if (lp > 0 && (deal || greedy)) {
+            int slot = 0;   // the last slot that starts at or before lid
+#pragma unroll
+            for (int step = kPlaceMax / 2; step >= 1; step >>= 1)
+                if (slot + step < NP && sm.first[slot + step] <= lid) slot += step;
+            bh = sm.place[slot] >> lp;
+            idx = (sm.place[slot] & (parts - 1)) + ((lid - sm.first[slot]) << lp);
+        } else {
+            const int slot = lid / nb;
+            bh = deal || greedy ? sm.place[slot] : slot;
+            idx = lid % nb;
+        }
+        const int blk = table == 0 ? nb - 1 - idx : idx;   // longest rows / first keys first
+        work = 0;
+        for (int u = 0; u < 2; ++u) {
+            const int m = 2 * blk + u;
+            if (m < M) {
+                work += table == 0 ? m - row_start[(size_t)bh * M + m] + 1
+                                   : col_end[(size_t)bh * M + m] - m + 1;
+            }
+        }
+        return bh * nb + blk;
+    };
+    for (int lid = lo + t; lid < hi; lid += THREADS) {
+        int work;
+        item(lid, work);
+        atomicAdd(&sm.hist[work], 1);
+    }
+    __syncthreads();
+    // Start of each count's run, largest count first: the bins in descending order,
+    // thread t owning positions [per t, per t + per) of that order.
+    {
+        const int per = (nbins + THREADS - 1) / THREADS;
+        const int e0 = min(per * t, nbins), e1 = min(e0 + per, nbins);
+        int tot = 0;
+        for (int e = e0; e < e1; ++e) tot += sm.hist[nbins - 1 - e];
+        int incl = tot;   // over the wave, then the waves before
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int v = __shfl_up(incl, off);
+            if ((t & 63) >= off) incl += v;
+        }
+        if ((t & 63) == 63) sm.wave[t >> 6] = incl;
+        __syncthreads();
+        int run = lo + incl - tot;
+        for (int w = 0; w < (t >> 6); ++w) run += sm.wave[w];
+        for (int e = e0; e < e1; ++e) {
+            const int cnt = sm.hist[nbins - 1 - e];
+            sm.hist[nbins - 1 - e] = run;
+            run += cnt;
+        }
+    }
+    __syncthreads();
+    for (int lid = lo + t; lid < hi; lid += THREADS) {
+        int work;
+        const int it = item(lid, work);
+        out[atomicAdd(&sm.hist[work], 1)] = it;
+    }
+}
+
+// Short sequences whose blocks are all resident at once need no table in the forward
+// (forward_direct): workgroup i takes block nb - 1 - i / BH of head i % BH + i / BH (mod
+// BH), so that every head's longest blocks start first and its blocks are spread over
+// the XCDs (workgroup i runs on XCD i % 8).  The tables, part of the plan and the
+// backward's order, are then filled by spare workgroups of the forward's own launch
+// instead of a kernel between stage 1 and it.
+__device__ __forceinline__ int direct_item(int i, int BH, int nb) {
+    const int blk = i / BH;
+    int bh = i - blk * BH + blk % BH;
+    bh -= bh >= BH ? BH : 0;
+    return bh * nb + nb - 1 - blk;
+}
+
+}  // namespace acp

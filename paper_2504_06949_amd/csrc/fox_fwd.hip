@@ -36,6 +36,7 @@
 
 #include "acp_device.h"
 #include "acp_internal.h"
+#include "acp_schedule.h"
 
 namespace acp {
 
@@ -443,11 +444,22 @@ __global__ __launch_bounds__(kFwdThreads * G) __attribute__((amdgpu_waves_per_eu
 void fwd_bf16_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
     const float* __restrict__ cg, const int* __restrict__ row_start,
-    const double* __restrict__ bound_u, const int* __restrict__ sched, __bf16* __restrict__ O,
+    const double* __restrict__ bound_u, ScheduleArgs sched, __bf16* __restrict__ O,
     float* __restrict__ lse, float* __restrict__ lse2, int L, int M, int nqb, int nblocks,
-    float kscale) {
+    float kscale, int direct) {
     __shared__ FwdSmem<D, G> sm;
-    const int item = sched[xcd_logical_id(blockIdx.x, nblocks)];   // bh * nqb + query block
+    static_assert(sizeof(sm) >= sizeof(ScheduleSmem), "the tables' scratch");
+    int item;   // bh * nqb + query block
+    if (direct) {
+        if ((int)blockIdx.x >= nblocks) {   // the 16 spare workgroups fill the tables
+            const int e = blockIdx.x - nblocks;
+            schedule_table<kFwdThreads * G>(reinterpret_cast<ScheduleSmem&>(sm), sched, e & 7, e >> 3);
+            return;
+        }
+        item = direct_item(blockIdx.x, sched.BH, nqb);
+    } else {
+        item = sched.sched_q[xcd_logical_id(blockIdx.x, nblocks)];
+    }
     const int bh = item / nqb;
     const double u_head = bound_u[bh];
     if (u_head <= kUFixedMax)
@@ -464,10 +476,11 @@ static void launch_fwd_bf16(const FwdArgs& a, int M, float kscale, hipStream_t s
     const int BH = a.B * a.H;
     const int nqb = (a.L + kFwdRows - 1) / kFwdRows;
     const int nblocks = BH * nqb;
-    hipLaunchKernelGGL((fwd_bf16_kernel<D, G>), dim3(nblocks), dim3(kFwdThreads * G), 0, s,
+    const int grid = nblocks + (a.direct ? 16 : 0);
+    hipLaunchKernelGGL((fwd_bf16_kernel<D, G>), dim3(grid), dim3(kFwdThreads * G), 0, s,
                        (const __bf16*)a.Q, (const __bf16*)a.K, (const __bf16*)a.V, a.c,
                        a.row_start, a.u, a.sched, (__bf16*)a.O, a.lse, a.lse2, a.L, M, nqb,
-                       nblocks, kscale);
+                       nblocks, kscale, a.direct ? 1 : 0);
 }
 
 hipError_t launch_fwd(const FwdArgs& a, hipStream_t s) {

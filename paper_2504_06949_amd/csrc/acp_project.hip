@@ -5,9 +5,9 @@
 //
 //   [Q | K] = X [Wq | Wk]     X [B*L, Dm], Wq and Wk [Dm, H*d] (row-major, bf16)
 //
-// One workgroup of 256 threads computes a 128 x 128 tile of the product with
-// bf16 MFMA (float32 accumulation), K-blocks of 64 staged through LDS by DMA and
-// double-buffered.  Its epilogue rounds the tile to bfloat16, writes every row
+// One workgroup computes a 128 x 128 tile of the product (256 threads), or 256 x 256
+// (512; project_big), with bf16 MFMA (float32 accumulation), K-blocks of 64 staged
+// through LDS by DMA and double-buffered.  Its epilogue rounds the tile to bfloat16, writes every row
 // straight into the head-split [B, H, L, d] layout, and forms, per head in the
 // tile, the largest float64 sum of squares of the stored row (ascending feature
 // order), which is the 128-row chunk maximum that rownorm_max_kernel would
@@ -17,7 +17,7 @@
 
 namespace acp {
 
-constexpr int kPrjTile = 128;   // rows (M) and columns (N) of a workgroup tile
+constexpr int kPrjCols = 128;   // columns of a block (one of Wq or of Wk)
 constexpr int kPrjK = 64;       // depth of one K-block
 
 // DMA of a 64 x 64*P bf16 block of a row-major matrix with row stride ld
@@ -64,53 +64,65 @@ struct StridedDma {
     }
 };
 
+// A workgroup's tile is MB blocks of 64 rows by NB blocks of 128 columns, its 4 NB waves
+// each taking 32 MB rows by 64 columns.
+template <int MB, int NB>
 struct PrjSmem {
+    static constexpr int kRows = 64 * MB, kCols = kPrjCols * NB;
     union {
         struct {
-            unsigned char a[2][2][64 * 128];   // X: two 64-row halves of 64 columns
-            unsigned char b[2][64 * 256];      // W: 64 rows x 128 columns (two panels)
+            unsigned char a[2][MB][64 * 128];   // X: 64-row blocks of 64 columns
+            unsigned char b[2][NB][64 * 256];   // W: 64 rows x 128 columns (two panels)
         } in;
-        __bf16 out[kPrjTile][kPrjTile + 8];   // the rounded tile, padded rows
+        __bf16 out[kRows][kCols + 8];           // the rounded tile, padded rows
     };
-    double rmax[2][4];
+    double rmax[2 * NB][MB];                    // per head of the tile and 64-row block
 };
 
-template <int D>
-__global__ __launch_bounds__(256) void qk_project_kernel(
+template <int D, int MB, int NB>
+__global__ __launch_bounds__(256 * NB) void qk_project_kernel(
     const __bf16* __restrict__ X, const __bf16* __restrict__ Wq, const __bf16* __restrict__ Wk,
-    int L, int Dm, int H, __bf16* __restrict__ Qo, __bf16* __restrict__ Ko,
+    int M, int L, int Dm, int H, __bf16* __restrict__ Qo, __bf16* __restrict__ Ko,
     double* __restrict__ part, int nchunk) {
-    __shared__ PrjSmem sm;
+    constexpr int kRows = PrjSmem<MB, NB>::kRows, kCols = PrjSmem<MB, NB>::kCols;
+    constexpr int kThreads = 256 * NB, kWaves = 4 * NB, kI = 2 * MB;
+    __shared__ PrjSmem<MB, NB> sm;
     const int HD = H * D;
-    // All column tiles of a 128-row block of X run on one XCD (a contiguous range
-    // of logical ids per XCD), so that the block is fetched into one L2 only.
-    const int ntn = 2 * H * D / kPrjTile;
+    // All column tiles of a row block of X run on one XCD (a contiguous range of
+    // logical ids per XCD), so that the block is fetched into one L2 only.
+    const int ntn = 2 * HD / kCols;
     const int lid = xcd_logical_id(blockIdx.x, gridDim.x);
     const int tn = lid % ntn, tm = lid / ntn;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = w >> 1, wn = w & 1;            // the wave's 64 x 64 quarter
+    const int wm = w / (2 * NB), wn = w % (2 * NB);   // the wave's half of the rows, its 64 columns
     const int g = lane >> 4, r16 = lane & 15;
-    const int m0 = tm * kPrjTile;
-    const int n0 = tn * kPrjTile;                 // column of [Q | K]
-    const int which = n0 / HD;                    // 0: Q, 1: K (a tile never straddles)
-    const __bf16* W = which == 0 ? Wq : Wk;
-    const int nw0 = n0 - which * HD;              // column inside Wq or Wk
+    const int m0 = tm * kRows;
+    // Column block j of the tile: 128 columns of [Q | K], of Wq or of Wk (H d is a
+    // multiple of 128, so a block never straddles)
+    auto which_of = [&](int j) { return tn * kCols + kPrjCols * j >= HD ? 1 : 0; };
+    auto col_of = [&](int j) { return tn * kCols + kPrjCols * j - which_of(j) * HD; };
 
-    StridedDma<1, 4> dma_a;
-    StridedDma<2, 4> dma_b;
+    StridedDma<1, kWaves> dma_a;
+    StridedDma<2, kWaves> dma_b;
     dma_a.init(w, lane, Dm);
     dma_b.init(w, lane, HD);
     auto issue = [&](int kb, int buf) __attribute__((always_inline)) {
         const int k0 = kb * kPrjK;
-        dma_a.issue(sm.in.a[buf][0], X + (size_t)m0 * Dm + k0, w);
-        dma_a.issue(sm.in.a[buf][1], X + (size_t)(m0 + 64) * Dm + k0, w);
-        dma_b.issue(sm.in.b[buf], W + (size_t)k0 * HD + nw0, w);
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+            // (a block past the last row reads the first again; M is a multiple of 128)
+            const int row = i < 2 || m0 + 64 * i < M ? m0 + 64 * i : m0;
+            dma_a.issue(sm.in.a[buf][i], X + (size_t)row * Dm + k0, w);
+        }
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+            dma_b.issue(sm.in.b[buf][j], (which_of(j) == 0 ? Wq : Wk) + (size_t)k0 * HD + col_of(j), w);
     };
 
-    f32x4 acc[4][4];
+    f32x4 acc[kI][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < kI; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
@@ -126,42 +138,41 @@ __global__ __launch_bounds__(256) void qk_project_kernel(
         __syncthreads();                          // block kb landed; block kb - 1 read
         const bool more = kb + 1 < nkb;
         if (more) issue(kb + 1, buf ^ 1);
-        const unsigned char* at = sm.in.a[buf][wm];
-        const unsigned char* bt = sm.in.b[buf];
+        const unsigned char* bt = sm.in.b[buf][wn >> 1];
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-            bf16x8 af[4], bfr[4];
+            bf16x8 af[kI], bfr[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) af[i] = tile_row8(at, 16 * i + r16, 32 * ks + 8 * g);
+            for (int i = 0; i < kI; ++i)
+                af[i] = tile_row8(sm.in.a[buf][(MB / 2) * wm + (i >> 2)], 16 * (i & 3) + r16, 32 * ks + 8 * g);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) bfr[j] = tile_col8(bt, 32 * ks + 8 * g, 64 * wn + 16 * j, r16);
+            for (int j = 0; j < 4; ++j) bfr[j] = tile_col8(bt, 32 * ks + 8 * g, 64 * (wn & 1) + 16 * j, r16);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < kI; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) acc[i][j] = mfma16(bfr[j], af[i], acc[i][j]);
-
         }
     }
 
     // ---- epilogue: the rounded tile through LDS ----------------------------------
     __syncthreads();                              // every wave is done with the inputs
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < kI; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             bf16x4 v;
             v[0] = (__bf16)acc[i][j][0]; v[1] = (__bf16)acc[i][j][1];
             v[2] = (__bf16)acc[i][j][2]; v[3] = (__bf16)acc[i][j][3];
-            *reinterpret_cast<bf16x4*>(&sm.out[64 * wm + 16 * i + r16][64 * wn + 16 * j + 4 * g]) = v;
+            *reinterpret_cast<bf16x4*>(&sm.out[32 * MB * wm + 16 * i + r16][64 * wn + 16 * j + 4 * g]) = v;
         }
     __syncthreads();
 
-    // largest sum of squares per head: thread t takes row t % 128 of the tile's
-    // head t / 128 (D = 64: two heads per tile; D = 128: one)
-    constexpr int kHeads = kPrjTile / D;
-    const int b = m0 / L, l0 = m0 % L;
-    {
-        const int row = tid & (kPrjTile - 1), hh = tid >> 7;
+    // Largest sum of squares per head of the tile and 64-row block: a thread per (row,
+    // head), a wave per 64 rows of one head
+    constexpr int kPerBlock = kPrjCols / D, kHeads = NB * kPerBlock;   // (D = 64: two heads per block)
+#pragma unroll
+    for (int k = 0; k < (kRows * kHeads + kThreads - 1) / kThreads; ++k) {
+        const int i = tid + kThreads * k, row = i % kRows, hh = i / kRows;
         double ss = 0.0;
         if (hh < kHeads) {
 #pragma unroll 2
@@ -174,41 +185,72 @@ __global__ __launch_bounds__(256) void qk_project_kernel(
                 }
             }
         }
-        // max over the 128 rows of the head (two waves)
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) ss = nan_max(ss, __shfl_xor(ss, off));
-        if (lane == 0) sm.rmax[hh][(tid >> 6) & 1] = ss;
+        if (lane == 0 && hh < kHeads) sm.rmax[hh][row >> 6] = ss;
     }
     __syncthreads();
-    if (tid < kHeads) {
-        const int h = nw0 / D + tid;
-        const double mx = nan_max(sm.rmax[tid][0], sm.rmax[tid][1]);
-        part[((size_t)(b * H + h) * 2 + which) * nchunk + l0 / kPrjTile] = mx;
-    }
-    // rows into [B, H, L, d]: 16-byte pieces, consecutive lanes along a row
-    __bf16* out = which == 0 ? Qo : Ko;
-    constexpr int kPieces = kPrjTile / 8;         // 16-byte pieces per tile row
-    for (int i = tid; i < kPrjTile * kPieces; i += 256) {
-        const int row = i / kPieces, pc = i % kPieces;
-        const int col = 8 * pc;                   // tile column
-        const int h = (nw0 + col) / D, e = (nw0 + col) % D;
-        const uint4 v = *reinterpret_cast<const uint4*>(&sm.out[row][col]);
-        *reinterpret_cast<uint4*>(out + (((size_t)b * H + h) * L + l0 + row) * D + e) = v;
+    // The tile in blocks of 128 rows by 128 columns, each of one sequence (L and M are
+    // multiples of 128) and of Q or K: everything but the row and piece is uniform.
+#pragma unroll
+    for (int c = 0; c < MB / 2; ++c) {
+        const int mc = m0 + 128 * c;
+        if (mc >= M) break;
+        const int b = mc / L, l0 = mc - b * L;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const int which = which_of(j), col0 = col_of(j), h0 = col0 / D;
+            if (tid < kPerBlock) {
+                const int hh = kPerBlock * j + tid;
+                part[((size_t)(b * H + h0 + tid) * 2 + which) * nchunk + l0 / 128] =
+                    nan_max(sm.rmax[hh][2 * c], sm.rmax[hh][2 * c + 1]);
+            }
+            // rows into [B, H, L, d]: 16-byte pieces, consecutive lanes along a row
+            __bf16* out = (which == 0 ? Qo : Ko) + (((size_t)b * H + h0) * L + l0) * D;
+            constexpr int kPieces = kPrjCols / 8;
+#pragma unroll
+            for (int k = 0; k < 128 * kPieces / kThreads; ++k) {
+                const int i = tid + kThreads * k, row = i / kPieces, col = 8 * (i % kPieces);
+                const uint4 v = *reinterpret_cast<const uint4*>(&sm.out[128 * c + row][kPrjCols * j + col]);
+                *reinterpret_cast<uint4*>(out + ((size_t)(col / D) * L + row) * D + col % D) = v;
+            }
+        }
     }
 }
 
+template <int D, int MB, int NB>
+static void project_t(const ProjectArgs& a, hipStream_t s) {
+    const int M = a.B * a.L, HD = a.H * a.d;
+    const int tiles = (2 * HD / (kPrjCols * NB)) * ((M + 64 * MB - 1) / (64 * MB));
+    hipLaunchKernelGGL((qk_project_kernel<D, MB, NB>), dim3(tiles), dim3(256 * NB), 0, s,
+                       (const __bf16*)a.X, (const __bf16*)a.Wq, (const __bf16*)a.Wk, M, a.L, a.Dm,
+                       a.H, (__bf16*)a.Q, (__bf16*)a.K, a.part, a.nchunk);
+}
+
+// The 256 x 256 tile or the 128 x 128 one.  The large tile reads half as much through L2
+// per product (the small one's loop is bound by that: 0.9 PFLOP/s), but a CU holds one
+// workgroup, whose prologue and epilogue nothing overlaps.  Measured, a round of large
+// tiles (256 at once) takes 1.75-1.95 of a round of small ones (512 at once) for a
+// d_model of 512 to 1536 and does the work of two, so the large tile is taken when the
+// rounds say so.  us, small -> large: 32768 x 1536 x 768 104 -> 98, 32768 x 2048 x 1024
+// 153 -> 139, 32768 x 3072 x 1536 346 -> 303, 16384 x 2048 x 1024 (d = 128) 80 -> 68, 8192
+// x 2048 x 1024 42.5 -> 41; against the rule: 8192 x 2560 x 1280 (320 tiles) 61 -> 78, 4096 x
+// 1536 x 768 (96) 20 -> 29.
+static bool project_big(int M, int N, int Dm) {
+    const int small = (M / 128) * (N / 128), large = ((M + 255) / 256) * (N / 256);
+    return Dm >= 512 && 19 * ((large + 255) / 256) <= 10 * ((small + 511) / 512);
+}
+
 hipError_t launch_qk_project(const ProjectArgs& a, hipStream_t s) {
-    const int HD = a.H * a.d;
-    dim3 grid((2 * HD / kPrjTile) * (a.B * a.L / kPrjTile));
     trace_begin(ACP_K_PROJECT, s);
-    if (a.d == 64)
-        hipLaunchKernelGGL(qk_project_kernel<64>, grid, dim3(256), 0, s, (const __bf16*)a.X,
-                           (const __bf16*)a.Wq, (const __bf16*)a.Wk, a.L, a.Dm, a.H,
-                           (__bf16*)a.Q, (__bf16*)a.K, a.part, a.nchunk);
-    else
-        hipLaunchKernelGGL(qk_project_kernel<128>, grid, dim3(256), 0, s, (const __bf16*)a.X,
-                           (const __bf16*)a.Wq, (const __bf16*)a.Wk, a.L, a.Dm, a.H,
-                           (__bf16*)a.Q, (__bf16*)a.K, a.part, a.nchunk);
+    const bool big = project_big(a.B * a.L, 2 * a.H * a.d, a.Dm);
+    if (a.d == 64) {
+        if (big) project_t<64, 4, 2>(a, s);
+        else project_t<64, 2, 1>(a, s);
+    } else {
+        if (big) project_t<128, 4, 2>(a, s);
+        else project_t<128, 2, 1>(a, s);
+    }
     const hipError_t e = hipGetLastError();
     if (e == hipSuccess) trace_end(ACP_K_PROJECT, s);
     return e;

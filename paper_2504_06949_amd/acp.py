@@ -250,14 +250,21 @@ def _dev(*ts):
     return ts[0].device
 
 
+# The current stream's address without a Stream object around it (0.2 us instead of
+# 2.0, of the 10 us of host time that a decoding step takes).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device) -> int:
+    if _raw_stream is not None and device.index is not None:
+        return _raw_stream(device.index)
     return torch.cuda.current_stream(device).cuda_stream
 
 
 def _shape(q: torch.Tensor):
     if q.dim() != 4:
         raise ValueError("Q/K/V must be [B, H, L, d]")
-    return tuple(int(s) for s in q.shape)
+    return tuple(q.shape)
 
 
 def workspace(q: torch.Tensor) -> torch.Tensor:
@@ -563,10 +570,11 @@ class Decoder:
         if self.t is None:
             raise RuntimeError("call init() first")
         dev = _dev(q, k, v, log_f, self.state)
+        rows, dtype = (self.B, self.H, self.d), self.dtype
         for name, x in (("q", q), ("k", k), ("v", v)):
-            if tuple(x.shape) != (self.B, self.H, self.d) or x.dtype != self.dtype:
+            if x.shape != rows or x.dtype != dtype:
                 raise ValueError(name + " must be [B, H, d] of the decoder's dtype")
-        if tuple(log_f.shape) != (self.B, self.H) or log_f.dtype != torch.float32:
+        if log_f.shape != rows[:2] or log_f.dtype != torch.float32:
             raise ValueError("log_f must be float32 [B, H]")
         if out is None:
             o = torch.empty_like(q)

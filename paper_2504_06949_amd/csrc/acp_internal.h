@@ -67,13 +67,16 @@ struct ScheduleArgs {
 // Blocks per head from which heads are placed in parts.
 constexpr int kLongBlocks = 32;
 // Whether the forward takes its blocks without the tables and fills them itself: as many
-// blocks as the CUs hold at once (4 per CU at d = 64, 2 at 128).  Beyond that the
+// blocks as the CUs hold at once (4 per CU at d = 64, 2 at 128), and at d = 128, whose
+// blocks take twice as long, short sequences only.  Beyond that the
 // tables' order and their keeping of a head on one XCD are worth their kernel.
 // Measured, us for the whole forward, tables first -> direct: 48 heads of 1024 tokens 43
 // -> 32, 100 of 640 37 -> 34; more blocks, forward kernel alone: 192 of 1024 (1536
 // blocks) 43 -> 47, 128 of 2048 (2048) 77 -> 92; d = 128, 32 of 3072 (768) 82 -> 92.
+// Long sequences: d = 64, 16 heads of 4096 72 -> 68, 5 of 5184 65 -> 60, 32 of 4096 98 ->
+// 91, 24 of 5120 106 -> 104, 12 of 8128 132 -> 130; d = 128, 8 of 8192 155 -> 168.
 inline bool forward_direct(int d, int nblocks, int nb) {
-    return nb < kLongBlocks && nblocks <= (d == 64 ? 1024 : 512);
+    return d == 64 ? nblocks <= 1024 : nblocks <= 512 && nb < kLongBlocks;
 }
 
 struct FwdArgs {

@@ -202,7 +202,7 @@ __device__ __forceinline__ void schedule_table(ScheduleSmem& sm, const ScheduleA
     }
 }
 
-// Short sequences whose blocks are all resident at once need no table in the forward
+// Calls whose blocks are all resident at once need no table in the forward
 // (forward_direct): workgroup i takes block nb - 1 - i / BH of head i % BH + i / BH (mod
 // BH), so that every head's longest blocks start first and its blocks are spread over
 // the XCDs (workgroup i runs on XCD i % 8).  The tables, part of the plan and the

@@ -10,8 +10,8 @@ namespace acp {
 // The attention kernels' workgroups each take 128 query rows (forward, dQ) or
 // 128 keys (dK/dV) of one head.  Workgroup ids are dealt round-robin to the 8
 // XCDs; xcd_logical_id turns that into a contiguous range of logical ids per XCD,
-// and this kernel fills, per XCD range, which (head, block) each logical id
-// takes, so that
+// and the tables say, per XCD range, which (head, block) each logical id takes, so
+// that
 //   - a head's workgroups run on one XCD (its K and V stay in one L2), or, when
 //     there are few long heads, on as few as a balanced load allows;
 //   - with at most kHeadsMax heads they are placed by kept-block count, largest
@@ -25,11 +25,9 @@ namespace acp {
 //   - otherwise they stay in bh order;
 //   - inside each XCD range the workgroups run largest first (a counting sort
 //     on their kept-tile counts), so that the range ends on small ones.
-// Grid (8, 2): x = XCD, y = 0 for the query-block table, 1 for the key-block one.
 // Entry = bh * nb + block.  Equal counts keep no particular order.
 constexpr int kHeadsMax = 64;          // heads that are placed
 constexpr int kPlaceMax = 256;         // parts that are dealt
-
 
 // log2 of the parts s per head: enough that the parts make whole rounds over the
 // XCDs, 8 (then every XCD has the same share of every head) for at most 16 heads, and
@@ -57,7 +55,7 @@ struct ScheduleSmem {
     int wave[16];
 };
 
-// One of the two tables for one XCD, by a workgroup of THREADS.
+// Table 0 (query blocks) or 1 (key blocks) for XCD x, by a workgroup of THREADS.
 template <int THREADS>
 __device__ __forceinline__ void schedule_table(ScheduleSmem& sm, const ScheduleArgs& a, int x, int table) {
     const int t = threadIdx.x, BH = a.BH, M = a.M, nb = a.nb;

@@ -25,6 +25,8 @@ def _lib():
     (1, 2, 1024, 64, (1.0, 8.0), 17.0, 74),
     (1, 2, 1088, 128, (1.0, 8.0), None, 75),   # d = 128: 2 groups
     (1, 2, 1024, 128, (3.0, 8.0), 21.0, 76),
+    (1, 1, 4160, 128, (5.0,), None, 77),       # the same through the schedule tables (33 blocks)
+    (1, 1, 4160, 64, (5.0,), None, 78),        # 4 groups of a long head, without them
     (1, 1, 960, 64, (5.0,), None, 77),         # 8 blocks, the last one ragged
     (1, 1, 896, 64, (5.0,), None, 78),         # 7 blocks: one group
 ])

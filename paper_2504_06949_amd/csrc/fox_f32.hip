@@ -82,6 +82,14 @@ struct ColOp {
     }
 };
 
+// Whether a logit of the lane is infinite or NaN: in every column of a subtile whose row
+// (of K in the dQ pass, of Q in the dK/dV pass) is, so that the rows themselves need a
+// look only where this says so.
+__device__ __forceinline__ bool any_nonfinite(const f32x4& s) {
+    return !__builtin_isfinite(s[0]) || !__builtin_isfinite(s[1]) || !__builtin_isfinite(s[2]) ||
+           !__builtin_isfinite(s[3]);
+}
+
 template <int D>
 __device__ __forceinline__ f32x4 row_product(const RowOp<D>& a, const RowOp<D>& b) {
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
@@ -384,21 +392,36 @@ void dq_f32_kernel(
     }
     for (; kt < kend; kt += kF32Waves) {
         rows_of(kt);
-        kc.load(Kh + (size_t)16 * kt * D, g, r);
         const f32x4 cj = ld4(ch + 16 * kt + 4 * g);
+        f32x4 ds[T];
+        bool odd = false;
 #pragma unroll
         for (int i = 0; i < T; ++i) {
             const int qt = q0 / 16 + i;
             if (kt <= qt) {
                 const f32x4 s = row_product<D>(kf, qf[i]);
+                odd = odd || any_nonfinite(s);
                 const f32x4 dp = row_product<D>(vf, gf[i]);
                 const int last = kt < qt ? 16 : r;
                 f32x4 p;
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
                     p[t] = fast_exp2(__builtin_fmaf(s[t], kscale, (ci[i] - cj[t]) * kLog2e) + l2d[i]);
-                const f32x4 ds = ds_of(i, p, dp, [&](int t) { return 4 * g + t <= last; });
-                col_product<D>(kc, ds, acc[i]);
+                ds[i] = ds_of(i, p, dp, [&](int t) { return 4 * g + t <= last; });
+            }
+        }
+        // (loaded last: next to the other operands it would cost a wave per SIMD)
+        kc.load(Kh + (size_t)16 * kt * D, g, r);
+        const bool bad = __ballot(odd) != 0ull && kc.take_nonfinite();
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            const int qt = q0 / 16 + i;
+            if (kt <= qt) {
+                col_product<D>(kc, ds[i], acc[i]);
+                const int last = kt < qt ? 16 : r;
+                if (bad)
+                    add_nonfinite<D>(Kh + (size_t)16 * kt * D, ds[i], acc[i], g, r,
+                                     [&](int key) { return key <= last; });
             }
         }
     }
@@ -487,6 +510,7 @@ void dkdv_f32_kernel(
         const f32x4 c4 = ld4(ch + 16 * qt + 4 * g), l4 = ld4(lh + 16 * qt + 4 * g),
                     d4 = ld4(dh + 16 * qt + 4 * g);
         f32x4 p[T], ds[T];
+        bool odd = false;
 #pragma unroll
         for (int i = 0; i < T; ++i) {
             const int kt = k0 / 16 + i;
@@ -494,6 +518,7 @@ void dkdv_f32_kernel(
             ds[i] = p[i];
             if (qt >= kt) {
                 const f32x4 s = row_product<D>(qr, kf[i]);
+                odd = odd || any_nonfinite(s);
                 const f32x4 dp = row_product<D>(gr, vf[i]);
                 const int first = qt > kt ? 0 : r;        // first query that keeps the lane's key
 #pragma unroll
@@ -518,9 +543,16 @@ void dkdv_f32_kernel(
                                      [&](int q) { return q >= first; });
             }
         oc.load(Qh + (size_t)16 * qt * D, g, r);
+        const bool bad_q = __ballot(odd) != 0ull && oc.take_nonfinite();
 #pragma unroll
         for (int i = 0; i < T; ++i)
-            if (qt >= k0 / 16 + i) col_product<D>(oc, ds[i], ak[i]);
+            if (qt >= k0 / 16 + i) {
+                col_product<D>(oc, ds[i], ak[i]);
+                const int first = qt > k0 / 16 + i ? 0 : r;
+                if (bad_q)
+                    add_nonfinite<D>(Qh + (size_t)16 * qt * D, ds[i], ak[i], g, r,
+                                     [&](int q) { return q >= first; });
+            }
     }
     for (; qt < qend; qt += kF32Waves) {
         rows_of(qt);

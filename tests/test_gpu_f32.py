@@ -66,3 +66,39 @@ def test_masked_nonfinite_values_do_not_leak(d):
         assert torch.equal(a[0, 1], b[0, 1])
     np.testing.assert_array_equal(got[2][0, 0, 71:].cpu().numpy(), want[2][0, 0, 71:].cpu().numpy())
     assert torch.isinf(got[2][0, 0, 70, 3])
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+@pytest.mark.parametrize("d", [64, 128])
+def test_masked_nonfinite_rows_do_not_leak_into_gradients(d, bad):
+    """A row of K that is not finite reaches dQ of the queries from its own on, and a
+    row of Q dK and dV of the keys up to its own: the other rows are those of the same
+    call without it (they mask it).  The bound comes from QK-norm scales, so that the
+    plan does not depend on the rows."""
+    w = workloads.custom("f32_nfg", 1, 2, 192, d, "f32", 92, mu=(2.0, 6.0))
+    print(f"case: {w.describe()} {bad}", flush=True)
+    g = to_gpu(workloads.generate(w))
+    gam = torch.full((2,), 1.5, device="cuda")
+
+    def grads(q, k):
+        o, _, ws = acp.forward_qknorm(q, k, g["v"], g["log_f"], gam, gam, EPS)
+        return acp.backward(q, k, g["v"], o, g["do"], ws)
+
+    want = grads(g["q"], g["k"])
+    for row, col in ((70, 5), (70, slice(None)), (143, 0)):
+        k = g["k"].clone()
+        k[0, 0, row, col] = bad
+        got = grads(g["q"], k)
+        assert torch.equal(got[0][0, 0, :row], want[0][0, 0, :row])
+        assert torch.isnan(got[0][0, 0, row]).any()
+        for a, b in zip(got[:3], want[:3]):
+            assert torch.equal(a[0, 1], b[0, 1])
+        q = g["q"].clone()
+        q[0, 0, row, col] = bad
+        got = grads(q, g["k"])
+        for a, b in zip(got[1:3], want[1:3]):
+            assert torch.equal(a[0, 0, row + 1:], b[0, 0, row + 1:])
+            assert torch.equal(a[0, 1], b[0, 1])
+        assert torch.isnan(got[1][0, 0, row]).any()
+        keep = [r for r in range(192) if r != row]
+        assert torch.equal(got[0][0, 0, keep], want[0][0, 0, keep])

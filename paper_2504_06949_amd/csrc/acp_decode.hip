@@ -263,8 +263,8 @@ __global__ __launch_bounds__(kPlanThreads) void decode_init_kernel(
 //      unnormalised O) with logits in log2 units, or max = -inf if it kept none.
 //   4. Workgroup 0 writes the state of position t: cum, pointer, flags, c_t, and
 //      k_t, v_t in slot t mod C.
-// kSingle: the keys fit one workgroup per head (256 keys, or 1024 with 1024 threads),
-// which then writes O and lse itself: no partial sums, no merge kernel.
+// kSingle: the keys fit one workgroup per head (256 keys, or 1024 with 1024 threads;
+// step_t), which then writes O and lse itself: no partial sums, no merge kernel.
 template <typename T, int D, int kThreads, bool kSingle>
 __global__ __launch_bounds__(kThreads) void decode_step_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
@@ -465,9 +465,11 @@ __global__ __launch_bounds__(kThreads) void decode_step_kernel(
                 pml[2 * sp + 1] = l;
             }
         }
-    } else if (tid == 0) {
-        pml[2 * sp] = -INFINITY;              // no kept key here: weight 0 in the merge
-        pml[2 * sp + 1] = 0.f;
+    } else if constexpr (!kSingle) {          // (a single workgroup holds key t, always kept)
+        if (tid == 0) {
+            pml[2 * sp] = -INFINITY;          // no kept key here: weight 0 in the merge
+            pml[2 * sp + 1] = 0.f;
+        }
     }
 
     // ---- 4. the state of position t ---------------------------------------------------
@@ -614,17 +616,23 @@ static void step_launch(const DecodeArgs& a, int nsplit, hipStream_t s) {
 template <typename T, int D>
 static hipError_t step_t(const DecodeArgs& a, hipStream_t s) {
     const int keys = min(a.t + 1, a.C), nsplit = (keys + kDecChunk - 1) / kDecChunk;
-    // One workgroup per head while it covers the keys: 256, or 1024 in bf16 (the float32
-    // kernel holds too many cache rows in registers for 16 waves).  A step is then one
-    // launch instead of two dependent ones: 96 heads, 100 tokens 11.4 -> 9.3 us, 500 tokens
-    // 13.2 -> 11.4, 940 tokens 13.3 -> 11.9 (256 heads 20.4 -> 19.6); at 1500 tokens two
-    // launches take 15.4.
+    // One workgroup per head while it covers the keys: 256 threads up to 256 keys, or 1024
+    // up to 1024 in bf16 (the float32 kernel holds too many cache rows in registers for 16
+    // waves) while there are no more heads than CUs, each of which holds one such
+    // workgroup.  A step is then one launch instead of two dependent ones.  Event timing
+    // with host launches, 96 heads (d = 64): 100 tokens 11.4 -> 9.3 us, 500 13.2 -> 11.4, 940
+    // 13.3 -> 11.9.  GPU alone (graph replay), two launches -> one, us:
+    //   d = 64: 12 heads 500 tokens 8.7 -> 8.7, 1000 8.7 -> 9.1; 256 heads 10.8 -> 9.6, 19.1 ->
+    //   16.5; d = 128: 12 heads 13.8 -> 12.7, 13.6 -> 13.6; 256 heads 21.2 -> 20.0, 27.5 -> 27.3;
+    //   beyond 256, a second round of workgroups: 320 heads (d = 64) 13.3 -> 18.4, 21.7 -> 24.5,
+    //   1024 28.3 -> 42.5, 47.6 -> 56.4, with most keys pruned 17.6 -> 30.1 and 29.0 -> 30.4;
+    //   d = 128, 320 heads 22.9 -> 32.7, 37.5 -> 40.8.
     if (nsplit == 1) {
         step_launch<T, D, kDecChunk, true>(a, 1, s);
         return hipGetLastError();
     }
     if constexpr (sizeof(T) == 2) {
-        if (keys <= 1024) {
+        if (keys <= 1024 && a.B * a.H <= 256) {
             step_launch<T, D, 1024, true>(a, 1, s);
             return hipGetLastError();
         }

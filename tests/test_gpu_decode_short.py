@@ -1,6 +1,6 @@
-"""Decoding across the key counts where a step changes its launch: one workgroup of
-256 keys per head, one of 1024, then several with a merge; and rings that keep the
-count there for any context.  Every step against the oracle (test_gpu_decode.py's
+"""Decoding across the key and head counts where a step changes its launch: one
+workgroup of 256 keys per head, one of 1024 (up to 256 heads), then several with a
+merge; and rings that keep the count there for any context.  Every step against the oracle (test_gpu_decode.py's
 checks and tolerances)."""
 import pytest
 
@@ -29,3 +29,14 @@ def _lib():
 def test_decode_launch_edges(dtype, d, L0, L, C):
     w = workloads.custom(f"edge{L0}_{C}", 1, 3, L, d, dtype, 97, mu=(2.0, 6.0, 12.0), qk_norm=True)
     _check(w, L0, C, EPS, 4 * L)
+
+
+@pytest.mark.parametrize("dtype,d,H,L0", [
+    ("bf16", 64, 256, 300),    # one workgroup of 1024 per head
+    ("bf16", 64, 257, 300),    # two of 256 and a merge
+    ("bf16", 128, 257, 300),
+    ("f32", 64, 257, 254),     # 255 .. 257 keys: one of 256, then two
+])
+def test_decode_many_heads(dtype, d, H, L0):
+    w = workloads.custom(f"heads{H}", 1, H, L0 + 3, d, dtype, 98, mu=(2.0, 6.0, 12.0), qk_norm=True)
+    _check(w, L0, 512, EPS, 2048)

@@ -12,7 +12,8 @@
 //   decode_init_kernel  prompt of L0 tokens -> delta, the running cumsum (a
 //                       double-double pair),
 //                       c of the prompt's last C positions, the pointer of query
-//                       L0 - 1; and the prompt's last K/V rows into the ring
+//                       L0 - 1; and the prompt's last K/V rows into the ring (or, by
+//                       size, decode_scan_kernel and decode_copy_kernel)
 //   decode_step_kernel  one token: c_t, the pointer advance, query t over its
 //                       kept keys (256 per workgroup, partial softmax sums), and
 //                       the append of k_t, v_t
@@ -43,8 +44,11 @@ size_t decode_partials_floats(int BH, int C, int d) {
 __device__ __forceinline__ int ring(int j, int C) { return j % C; }
 
 // ---------------------------------------------------------------------------
-// The state of head bh after the prompt, by one workgroup.
-template <int D>
+// The state of head bh after the prompt, by one workgroup of 1024 threads, each of which
+// holds kHeld values of its run at a time.  kHeld = 4 is a whole run of a prompt of up to
+// 4096 tokens, and two workgroups then fit a CU (kRunHeld takes 70 VGPRs, one too many
+// for 64 per lane).
+template <int D, int kHeld>
 __device__ __forceinline__ void decode_init_head(
     int bh, int BH, const float* __restrict__ log_f,
     const float* __restrict__ gamma_q, const float* __restrict__ gamma_k, int H, int L0, int C,
@@ -77,7 +81,7 @@ __device__ __forceinline__ void decode_init_head(
     const int per = run_length(L0);
     const int beg = min(t * per, L0), n = min(beg + per, L0) - beg;
     const bool vec = (L0 & 3) == 0;   // every head's row is whole float4s
-    float xv[kRunHeld];               // the first batch (all of the run if per <= kRunHeld)
+    float xv[kHeld];               // the first batch (all of the run if per <= kHeld)
     load_run(x + beg, 0, n, vec, xv);
     // float64 first, double-double for a head whose sums span 53 bits or more (the
     // rule of the plan kernel, which explains it)
@@ -85,7 +89,7 @@ __device__ __forceinline__ void decode_init_head(
     int min_lsb = 1 << 30;
     for (int b = 0;;) {
 #pragma unroll
-        for (int i = 0; i < kRunHeld; ++i) {
+        for (int i = 0; i < kHeld; ++i) {
             if (b + i < n) {
                 const float v = xv[i];
                 if (!__builtin_isfinite(v)) flags |= 2;
@@ -97,7 +101,7 @@ __device__ __forceinline__ void decode_init_head(
                 local_abs += __builtin_fabs((double)v);
             }
         }
-        b += kRunHeld;
+        b += kHeld;
         if (b >= n) break;
         load_run(x + beg, b, n, vec, xv);
     }
@@ -115,11 +119,11 @@ __device__ __forceinline__ void decode_init_head(
     }
     auto emit = [&](auto run) __attribute__((always_inline)) {
         float* ring_c = cc + (size_t)bh * C;
-        for (int b = 0; b < n; b += kRunHeld) {
-            if (per > kRunHeld) load_run(x + beg, b, n, vec, xv);
+        for (int b = 0; b < n; b += kHeld) {
+            if (per > kHeld) load_run(x + beg, b, n, vec, xv);
             // C and the run's start are multiples of 4, so four positions never wrap
 #pragma unroll
-            for (int q = 0; q < kRunHeld; q += 4) {
+            for (int q = 0; q < kHeld; q += 4) {
                 const int i0 = beg + b + q;
                 const int slot = i0 % C;
                 float4 c4;
@@ -150,10 +154,10 @@ __device__ __forceinline__ void decode_init_head(
     };
     if (wide) {
         DD l{0.0, 0.0}, la{0.0, 0.0};
-        for (int b = 0; b < n; b += kRunHeld) {
-            if (per > kRunHeld) load_run(x + beg, b, n, vec, xv);
+        for (int b = 0; b < n; b += kHeld) {
+            if (per > kHeld) load_run(x + beg, b, n, vec, xv);
 #pragma unroll
-            for (int i = 0; i < kRunHeld; ++i) {
+            for (int i = 0; i < kHeld; ++i) {
                 if (b + i < n) {
                     l = dd_add(l, (double)xv[i]);
                     la = dd_add(la, __builtin_fabs((double)xv[i]));
@@ -192,27 +196,26 @@ __device__ __forceinline__ void decode_init_head(
     }
 }
 
-// The prompt's last min(L0, C) K and V rows into their ring slots: kCopyRows rows of
-// both tensors per workgroup, every lane's 16-byte pieces requested before any is
+// The prompt's last min(L0, C) K and V rows into their ring slots: a quarter of kThreads
+// rows of both tensors per workgroup, every lane's 16-byte pieces requested before any is
 // stored.
-constexpr int kCopyRows = 4 * 64;
-
-template <typename T, int D>
+template <typename T, int D, int kThreads>
 __device__ __forceinline__ void decode_copy_rows(
     int bh, int chunk, const T* __restrict__ K, const T* __restrict__ V, int L0, int C,
     T* __restrict__ Kc, T* __restrict__ Vc) {
+    constexpr int kRows = kThreads / 4;
     constexpr int kVec = 16 / (int)sizeof(T);
-    constexpr int kPerRow = D / kVec;                           // 16-byte pieces per row
-    constexpr int kPer = kCopyRows * kPerRow / kPlanThreads;    // pieces per thread and tensor
+    constexpr int kPerRow = D / kVec;                       // 16-byte pieces per row
+    constexpr int kPer = kRows * kPerRow / kThreads;        // pieces per thread and tensor
     const int t = threadIdx.x;
     const int j0 = max(0, L0 - C);
-    const int r0 = j0 + chunk * kCopyRows;
-    const int c0 = r0 % C;   // (kCopyRows can exceed C: a full modulo per row)
+    const int r0 = j0 + chunk * kRows;
+    const int c0 = r0 % C;   // (kRows can exceed C: a full modulo per row)
     uint4 kv[kPer], vv[kPer];
 #pragma unroll
     for (int p = 0; p < kPer; ++p) {
         // rows past the prompt read its last row again (branch-free)
-        const int i = t + kPlanThreads * p, j = min(r0 + i / kPerRow, L0 - 1), e = (i % kPerRow) * kVec;
+        const int i = t + kThreads * p, j = min(r0 + i / kPerRow, L0 - 1), e = (i % kPerRow) * kVec;
         const size_t src = ((size_t)bh * L0 + j) * D + e;
         kv[p] = *reinterpret_cast<const uint4*>(K + src);
         vv[p] = *reinterpret_cast<const uint4*>(V + src);
@@ -221,19 +224,16 @@ __device__ __forceinline__ void decode_copy_rows(
 #pragma unroll
     for (int p = 0; p < kPer; ++p) {
         // (a row past the prompt rewrites the last row's slot with the same bytes)
-        const int i = t + kPlanThreads * p, j = min(r0 + i / kPerRow, L0 - 1), e = (i % kPerRow) * kVec;
+        const int i = t + kThreads * p, j = min(r0 + i / kPerRow, L0 - 1), e = (i % kPerRow) * kVec;
         const size_t dst = ((size_t)bh * C + (c0 + (j - r0)) % C) * D + e;
         *reinterpret_cast<uint4*>(Kc + dst) = kv[p];
         *reinterpret_cast<uint4*>(Vc + dst) = vv[p];
     }
 }
 
-// One launch for both: workgroups 0 .. B*H - 1 a head's scan each, the others the
-// rows (nothing orders them against each other).  The scans, one workgroup per head
-// and bound by latency, run beside the copy, which the memory bounds: as two
-// launches 8 + 32 us for 96 heads of 4096 tokens, 145 + 567 for 65536 (the scan then
-// read value by value); as one 33 and 607 (event timing; two launches 39 and 711).
-template <typename T, int D>
+// One launch for both (init_held_t): workgroups 0 .. B*H - 1 a head's scan each, the others
+// the rows (nothing orders them against each other).
+template <typename T, int D, int kHeld>
 __global__ __launch_bounds__(kPlanThreads) void decode_init_kernel(
     const T* __restrict__ K, const T* __restrict__ V, const float* __restrict__ log_f,
     const float* __restrict__ gamma_q, const float* __restrict__ gamma_k, int BH, int H, int L0,
@@ -242,10 +242,30 @@ __global__ __launch_bounds__(kPlanThreads) void decode_init_kernel(
     double* __restrict__ delta_out, int* __restrict__ flags_out) {
     const int b = blockIdx.x;
     if (b < BH)
-        decode_init_head<D>(b, BH, log_f, gamma_q, gamma_k, H, L0, C, log_lmax_over_eps, cc,
-                            cs_out, ptr_out, delta_out, flags_out);
+        decode_init_head<D, kHeld>(b, BH, log_f, gamma_q, gamma_k, H, L0, C, log_lmax_over_eps, cc,
+                                   cs_out, ptr_out, delta_out, flags_out);
     else
-        decode_copy_rows<T, D>((b - BH) / nchunks, (b - BH) % nchunks, K, V, L0, C, Kc, Vc);
+        decode_copy_rows<T, D, kPlanThreads>((b - BH) / nchunks, (b - BH) % nchunks, K, V, L0, C, Kc, Vc);
+}
+
+// Or a launch each (init_held_t)
+template <int D, int kHeld>
+__global__ __launch_bounds__(kPlanThreads) void decode_scan_kernel(
+    const float* __restrict__ log_f, const float* __restrict__ gamma_q,
+    const float* __restrict__ gamma_k, int H, int L0, int C, double log_lmax_over_eps,
+    float* __restrict__ cc, double* __restrict__ cs_out, int* __restrict__ ptr_out,
+    double* __restrict__ delta_out, int* __restrict__ flags_out) {
+    decode_init_head<D, kHeld>(blockIdx.x, gridDim.x, log_f, gamma_q, gamma_k, H, L0, C,
+                               log_lmax_over_eps, cc, cs_out, ptr_out, delta_out, flags_out);
+}
+
+constexpr int kCopyThreads = 256;
+
+template <typename T, int D>
+__global__ __launch_bounds__(kCopyThreads) void decode_copy_kernel(
+    const T* __restrict__ K, const T* __restrict__ V, int L0, int C, T* __restrict__ Kc,
+    T* __restrict__ Vc) {
+    decode_copy_rows<T, D, kCopyThreads>(blockIdx.y, blockIdx.x, K, V, L0, C, Kc, Vc);
 }
 
 // ---------------------------------------------------------------------------
@@ -586,14 +606,39 @@ __global__ __launch_bounds__(THREADS) void decode_combine_kernel(
 }
 
 // ---------------------------------------------------------------------------
+template <typename T, int D, int kHeld>
+static hipError_t init_held_t(const DecodeInitArgs& a, hipStream_t s) {
+    const int BH = a.B * a.H, rows = min(a.L0, a.C);
+    // One launch or two.  In one, the scans, a workgroup per head and bound by latency, run
+    // beside the copy, which the memory bounds, but the copy's workgroups are the scan's
+    // size, 256 rows, and with many heads a last one that is nearly empty costs more than
+    // the launch.  GPU time (graph replay), two launches -> one, us: 1 head of 65536 tokens
+    // (d = 64) 122 -> 45, 12 of 4096 10.8 -> 7.0, 96 of 4096 40 -> 34, 320 of 300 14.8 -> 12.3, 1024
+    // of 200 29.9 -> 24.7, 4096 of 100 66 -> 60; but 512 of 300 (44 rows in the last) 19.4 ->
+    // 19.8, d = 128 31 -> 33, 1024 of 300 at d = 128 62 -> 72, 4096 of 257 138 -> 148, of 1 35 -> 44.
+    constexpr int kRows = kPlanThreads / 4;
+    if (BH <= 384 || (rows - 1) % kRows + 1 >= 96) {
+        const int nchunks = (rows + kRows - 1) / kRows;
+        hipLaunchKernelGGL((decode_init_kernel<T, D, kHeld>), dim3(BH + BH * nchunks),
+                           dim3(kPlanThreads), 0, s, (const T*)a.K, (const T*)a.V, a.log_f, a.gamma_q,
+                           a.gamma_k, BH, a.H, a.L0, a.C, nchunks, a.log_lmax_over_eps, (T*)a.Kc,
+                           (T*)a.Vc, a.cc, a.cs, a.ptr, a.delta, a.flags);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((decode_scan_kernel<D, kHeld>), dim3(BH), dim3(kPlanThreads), 0, s, a.log_f,
+                       a.gamma_q, a.gamma_k, a.H, a.L0, a.C, a.log_lmax_over_eps, a.cc, a.cs, a.ptr,
+                       a.delta, a.flags);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((decode_copy_kernel<T, D>), dim3((rows + kCopyThreads / 4 - 1) / (kCopyThreads / 4), BH),
+                       dim3(kCopyThreads), 0, s, (const T*)a.K, (const T*)a.V, a.L0, a.C, (T*)a.Kc,
+                       (T*)a.Vc);
+    return hipGetLastError();
+}
+
 template <typename T, int D>
 static hipError_t init_t(const DecodeInitArgs& a, hipStream_t s) {
-    const int BH = a.B * a.H, nchunks = (min(a.L0, a.C) + kCopyRows - 1) / kCopyRows;
-    hipLaunchKernelGGL((decode_init_kernel<T, D>), dim3(BH + BH * nchunks), dim3(kPlanThreads), 0, s,
-                       (const T*)a.K, (const T*)a.V, a.log_f, a.gamma_q, a.gamma_k, BH, a.H, a.L0,
-                       a.C, nchunks, a.log_lmax_over_eps, (T*)a.Kc, (T*)a.Vc, a.cc, a.cs, a.ptr,
-                       a.delta, a.flags);
-    return hipGetLastError();
+    return a.L0 <= 4 * kPlanThreads ? init_held_t<T, D, 4>(a, s) : init_held_t<T, D, kRunHeld>(a, s);
 }
 
 hipError_t launch_decode_init(const DecodeInitArgs& a, hipStream_t s) {

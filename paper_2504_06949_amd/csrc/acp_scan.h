@@ -17,21 +17,22 @@ constexpr int kRunHeld = 16;
 // every run is whole float4s (n itself being a multiple of 4).
 __device__ __forceinline__ int run_length(int n) { return (n + 4 * kPlanThreads - 1) / (4 * kPlanThreads) * 4; }
 
-// x[i .. i + kRunHeld) of a run of n values into v, zeros past its end; all loads are
+// x[i .. i + N) of a run of n values into v, zeros past its end; all loads are
 // requested before any is waited for.  `vec`: n and i are multiples of 4 and x is
 // 16-byte aligned.
+template <int N>
 __device__ __forceinline__ void load_run(const float* __restrict__ x, int i, int n, bool vec,
-                                         float (&v)[kRunHeld]) {
+                                         float (&v)[N]) {
     if (vec) {
 #pragma unroll
-        for (int k = 0; k < kRunHeld; k += 4) {
+        for (int k = 0; k < N; k += 4) {
             float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
             if (i + k < n) q = *reinterpret_cast<const float4*>(x + i + k);
             v[k] = q.x; v[k + 1] = q.y; v[k + 2] = q.z; v[k + 3] = q.w;
         }
     } else {
 #pragma unroll
-        for (int k = 0; k < kRunHeld; ++k) v[k] = i + k < n ? x[i + k] : 0.f;
+        for (int k = 0; k < N; ++k) v[k] = i + k < n ? x[i + k] : 0.f;
     }
 }
 

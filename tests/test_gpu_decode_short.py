@@ -40,3 +40,15 @@ def test_decode_launch_edges(dtype, d, L0, L, C):
 def test_decode_many_heads(dtype, d, H, L0):
     w = workloads.custom(f"heads{H}", 1, H, L0 + 3, d, dtype, 98, mu=(2.0, 6.0, 12.0), qk_norm=True)
     _check(w, L0, 512, EPS, 2048)
+
+
+@pytest.mark.parametrize("dtype,d,H,L0,C", [
+    ("bf16", 64, 384, 257, 320),   # the set-up in one launch, its last workgroup with one row
+    ("bf16", 64, 385, 257, 320),   # in two
+    ("f32", 128, 385, 65, 64),     # in two, a ring shorter than the prompt
+    ("bf16", 128, 385, 96, 128),   # in one
+    ("bf16", 64, 1, 4097, 4160),   # a run of 8 positions per thread
+])
+def test_decode_setup_launches(dtype, d, H, L0, C):
+    w = workloads.custom(f"setup{H}", 1, H, L0 + 1, d, dtype, 99, mu=(2.0, 6.0, 12.0), qk_norm=True)
+    _check(w, L0, C, EPS, 2 * L0)

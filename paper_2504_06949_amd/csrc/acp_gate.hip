@@ -80,7 +80,7 @@ __device__ __forceinline__ double bits_f64(unsigned long long b) {
 // The logits' reduction order is fixed (ascending features, every step rounded once),
 // so each (token, head) is one chain of d_model dependent multiply-adds, and the kernel
 // is bound by how few instructions and cycles a feature takes:
-//   * up to 16 heads, on the VALU: lane l takes token 16 w + l / 4 and the N heads
+//   * up to 20 heads, on the VALU: lane l takes token 16 w + l / 4 and the N heads
 //     l % 4 + 4 q, with the weights as float32 in LDS: one conversion and N multiply-adds
 //     per feature, all operands per lane (no broadcast).
 //   * more heads, on the matrix cores, one feature at a time:
@@ -90,12 +90,14 @@ __device__ __forceinline__ double bits_f64(unsigned long long b) {
 //     and heads 4 j .. + 3 of a group of 16: lane l holds the features of token
 //     4 (l / 16) + l % 4 and the weights of head l % 16, and ends with the logits of tokens
 //     4 (l / 16) + (0..3), head l % 16.  A dependent one takes about 44 cycles, whatever the
-//     number of heads, which is why fewer go to the VALU.
+//     number of heads in its group of 16, which is why fewer go to the VALU: 4096 tokens
+//     of d_model 4096, 20 heads 112 us there, 21 to 32 on the matrix cores 143.  Only groups
+//     that hold heads are formed: 48 heads 186 us in 3 groups, 258 in 4.
 //
 // Measured with the set-up kernel (event timing, us) against the earlier form (a lane per
 // token and 4 heads per wave, weights broadcast from LDS, one look-back after the other):
 // 32768 tokens of d_model 768: 4 heads 33.7 -> 24.0, 8 38.6 -> 29.3, 12 41.9 -> 36.0, 16
-// 44.4 -> 41.8, 20 63.6 -> 59.0; 1088 tokens of 1088, 24 heads 62.2 -> 54.0.  12 heads on
+// 44.4 -> 41.8, 20 59 -> 46, 33 81 -> 77, 48 97 -> 87 (the last three by graph replay); 1088 tokens of 1088, 24 heads 62.2 -> 54.0.  12 heads on
 // the matrix cores: 38.5.  X alone is 50 MB, 10 us at the copy rate; 20 of the 36 us are the
 // two launches, log f and the look-back (measured at d_model 64).
 constexpr int kGateThreads = 256;
@@ -424,7 +426,9 @@ hipError_t launch_gate(const GateArgs& a, hipStream_t s) {
     else if (a.H <= 8) gate_t<2, false>(a, s);
     else if (a.H <= 12) gate_t<3, false>(a, s);
     else if (a.H <= 16) gate_t<4, false>(a, s);
+    else if (a.H <= 20) gate_t<5, false>(a, s);
     else if (a.H <= 32) gate_t<2, true>(a, s);
+    else if (a.H <= 48) gate_t<3, true>(a, s);
     else gate_t<4, true>(a, s);
     e = hipGetLastError();
     trace_end(ACP_K_GATE, s);

@@ -229,16 +229,19 @@ static void project_t(const ProjectArgs& a, hipStream_t s) {
 
 // The 256 x 256 tile or the 128 x 128 one.  The large tile reads half as much through L2
 // per product (the small one's loop is bound by that: 0.9 PFLOP/s), but a CU holds one
-// workgroup, whose prologue and epilogue nothing overlaps.  Measured, a round of large
-// tiles (256 at once) takes 1.75-1.95 of a round of small ones (512 at once) for a
-// d_model of 512 to 1536 and does the work of two, so the large tile is taken when the
-// rounds say so.  us, small -> large: 32768 x 1536 x 768 104 -> 98, 32768 x 2048 x 1024
-// 153 -> 139, 32768 x 3072 x 1536 346 -> 303, 16384 x 2048 x 1024 (d = 128) 80 -> 68, 8192
-// x 2048 x 1024 42.5 -> 41; against the rule: 8192 x 2560 x 1280 (320 tiles) 61 -> 78, 4096 x
-// 1536 x 768 (96) 20 -> 29.
+// workgroup, whose prologue and epilogue nothing overlaps.  Measured over 400 shapes
+// (d_model 512 to 2048, 60 to 1500 large tiles), a round of large tiles (256 at once), which
+// does the work of two of the small ones (512 at once), takes 1.6 + 165 / d_model of one, and a
+// last round of at most 256 small tiles, one to a CU, 0.6.  With that the tile taken is the
+// slower one by more than 3% in 12 of them (at most 9%).  us, small -> large: 32768 x 1536 x
+// 768 104 -> 98, 32768 x 2048 x 1024 153 -> 139, 32768 x 3072 x 1536 346 -> 303, 16384 x 2048 x
+// 1024 (d = 128) 80 -> 68; against the rule: 8192 x 2560 x 1280 (320 large tiles) 61 -> 78, 4096 x
+// 1536 x 768 (96) 20 -> 29, 28672 x 2048 x 512 (896) 72.8 -> 79.3, 8192 x 1536 x 512 (192) 21 -> 24.
 static bool project_big(int M, int N, int Dm) {
     const int small = (M / 128) * (N / 128), large = ((M + 255) / 256) * (N / 256);
-    return Dm >= 512 && 19 * ((large + 255) / 256) <= 10 * ((small + 511) / 512);
+    const int rest = small % 512;
+    const double rounds = small / 512 + (rest == 0 ? 0.0 : rest <= 256 ? 0.6 : 1.0);
+    return Dm >= 512 && (1.6 + 165.0 / Dm) * ((large + 255) / 256) <= rounds;
 }
 
 hipError_t launch_qk_project(const ProjectArgs& a, hipStream_t s) {

@@ -13,16 +13,17 @@ namespace acp {
 // and the tables say, per XCD range, which (head, block) each logical id takes, so
 // that
 //   - a head's workgroups run on one XCD (its K and V stay in one L2), or, when
-//     there are few long heads, on as few as a balanced load allows;
-//   - with at most kHeadsMax heads they are placed by kept-block count, largest
-//     first, each on the least loaded XCD that still has room (the same number per
-//     XCD).  What is placed are whole heads when sequences are short (below 32 of the
-//     128-row blocks), else parts of a head, every s-th of its blocks
-//     (schedule_log_parts); 8 parts per head are simply dealt out, one to each XCD.
+//     there are few long heads of unequal work, on as few as a balanced load allows;
+//   - at most kHeadsMax heads whose number is a multiple of 8 are placed by kept-block
+//     count, largest first, each on the least loaded XCD that still has room (the same
+//     number per XCD).
 //     (With more heads an XCD has several of them, and reading the counts first
 //     costs this kernel 3 us: 96 heads of 4096 tokens 6.4 -> 9.3, the forward 187
 //     either way.)
-//   - otherwise they stay in bh order;
+//   - long heads (32 or more of the 128-row blocks) are placed in parts, every s-th of a
+//     head's blocks (schedule_log_parts), unless whole heads already load the XCDs
+//     evenly (schedule_even); 8 parts per head are simply dealt out, one to each XCD;
+//   - otherwise (other numbers of heads) they stay in bh order;
 //   - inside each XCD range the workgroups run largest first (a counting sort
 //     on their kept-tile counts), so that the range ends on small ones.
 // Entry = bh * nb + block.  Equal counts keep no particular order.
@@ -39,6 +40,7 @@ constexpr int kPlaceMax = 256;         // parts that are dealt
 // loaded XCD: every kernel 2% slower.)  Training step at 4 x 16 heads of 8192 tokens: 1.73 ms
 // undivided, 1.77 in 2 parts, 1.83 in 4; 2 x 16 heads of 16384 (d = 128): 5.12 ms in 2
 // parts, 5.18 in 4, 5.30 in 8.
+// (33 to 63 heads that are no multiple of 8 would make more than 64 parts: in bh order.)
 __host__ __device__ constexpr int schedule_log_parts(int BH, int nb) {
     if (nb < kLongBlocks) return 0;
     int s = 0;
@@ -46,7 +48,15 @@ __host__ __device__ constexpr int schedule_log_parts(int BH, int nb) {
     return BH << s <= kHeadsMax ? s : BH <= kHeadsMax / 2 ? 3 : 0;
 }
 
+// Heads of equal work gain nothing from parts and pay for them in L2: unpruned, 16 heads of
+// 16384 tokens (d = 128) forward 1034 us in whole heads, 1161 in parts, backward 3169 and
+// 3472; 32 of 8192 549 and 590; 20 of 8192 (d = 64), each pruned to 3 tiles per row, 44 and 51.
+// So they are divided only if the heaviest XCD would carry more than this over the average.
+constexpr float kEvenLoad = 1.05f;
+
 struct ScheduleSmem {
+    int sorted[kHeadsMax];                           // kept counts, largest first
+    int load[8];                                     // kept tiles per XCD
     int place[kPlaceMax];                            // part of each slot: bh * parts + part
     int first[kPlaceMax + 1];                        // first logical id of each slot
     __attribute__((aligned(16))) int kept[kPlaceMax];
@@ -55,16 +65,70 @@ struct ScheduleSmem {
     int wave[16];
 };
 
+// The range of logical ids of XCD x (as xcd_logical_id deals them)
+__device__ __forceinline__ void schedule_range(int nblocks, int x, int& lo, int& hi) {
+    const int q = nblocks >> 3, r = nblocks & 7;
+    lo = x * q + min(x, r);
+    hi = lo + q + (x < r ? 1 : 0);
+}
+
+// Kept tiles of a 128-row block in table 0 (queries) or 1 (keys)
+__device__ __forceinline__ int schedule_work(const ScheduleArgs& a, int table, int bh, int blk) {
+    int work = 0;
+    for (int u = 0; u < 2; ++u) {
+        const int m = 2 * blk + u;
+        if (m < a.M) {
+            work += table == 0 ? m - a.row_start[(size_t)bh * a.M + m] + 1
+                               : a.col_end[(size_t)bh * a.M + m] - m + 1;
+        }
+    }
+    return work;
+}
+
+// Whether whole heads load the XCDs evenly: BH a multiple of 8, sorted by count and dealt
+// back and forth (placing them by load does no worse); else the ranges of the bh order,
+// summed block by block.  sm.kept holds the counts; the answer is uniform and the same in
+// every workgroup of the table.
+template <int THREADS, typename Rank>
+__device__ __forceinline__ bool schedule_even(ScheduleSmem& sm, const ScheduleArgs& a, int table, Rank rank_of) {
+    const int t = threadIdx.x, lane = t & 63, BH = a.BH;
+    if (BH % 8 == 0) {
+        if (t < BH) sm.sorted[rank_of(t)] = sm.kept[t];
+        __syncthreads();
+        if (t < 8) {
+            int sum = 0;
+            for (int j = 0; 8 * j < BH; ++j) sum += sm.sorted[8 * j + (j & 1 ? 7 - t : t)];
+            sm.load[t] = sum;
+        }
+    } else {
+        for (int x = t >> 6; x < 8; x += THREADS / 64) {
+            int lo, hi, sum = 0;
+            schedule_range(BH * a.nb, x, lo, hi);
+            for (int lid = lo + lane; lid < hi; lid += 64) {
+                const int idx = lid % a.nb;
+                sum += schedule_work(a, table, lid / a.nb, table == 0 ? a.nb - 1 - idx : idx);
+            }
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+            if (lane == 0) sm.load[x] = sum;
+        }
+    }
+    __syncthreads();
+    int most = 0;
+    float total = 0.f;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+        most = max(most, sm.load[x]);
+        total += (float)sm.load[x];
+    }
+    return 8.f * (float)most <= kEvenLoad * total;
+}
+
 // Table 0 (query blocks) or 1 (key blocks) for XCD x, by a workgroup of THREADS.
 template <int THREADS>
 __device__ __forceinline__ void schedule_table(ScheduleSmem& sm, const ScheduleArgs& a, int x, int table) {
     const int t = threadIdx.x, BH = a.BH, M = a.M, nb = a.nb;
     const long long* kept = a.kept;
-    const int* row_start = a.row_start;
-    const int* col_end = a.col_end;
-    const int lp = schedule_log_parts(BH, nb), parts = 1 << lp, NP = BH << lp;
-    const bool deal = lp == 3 && BH <= kHeadsMax / 2;    // NP a multiple of 8, <= kPlaceMax
-    const bool greedy = !deal && NP % 8 == 0 && NP <= kHeadsMax;
     // the head's rank by kept count (largest first, ties by index)
     auto rank_of = [&](int bh) {
         const int mine = sm.kept[bh];
@@ -79,8 +143,14 @@ __device__ __forceinline__ void schedule_table(ScheduleSmem& sm, const ScheduleA
         return rank;
     };
     static_assert(THREADS >= kPlaceMax, "a thread per part");
-    if ((deal || greedy) && t < kPlaceMax) sm.kept[t] = t < BH ? (int)min(max(kept[t], 0ll), 1ll << 22) : -1;
+    if (BH <= kHeadsMax && (BH % 8 == 0 || schedule_log_parts(BH, nb) > 0) && t < kPlaceMax)
+        sm.kept[t] = t < BH ? (int)min(max(kept[t], 0ll), 1ll << 22) : -1;
     __syncthreads();
+    int lp = schedule_log_parts(BH, nb);                 // (0 beyond kHeadsMax heads)
+    if (lp > 0 && schedule_even<THREADS>(sm, a, table, rank_of)) lp = 0;
+    const int parts = 1 << lp, NP = BH << lp;
+    const bool deal = lp == 3 && BH <= kHeadsMax / 2;    // NP a multiple of 8, <= kPlaceMax
+    const bool greedy = !deal && NP % 8 == 0 && NP <= kHeadsMax;
     if (deal) {
         // slot (NP / 8) j + i: part j of the head of rank i
         if (t < NP) sm.place[BH * (t & 7) + rank_of(t >> 3)] = t;
@@ -133,9 +203,8 @@ __device__ __forceinline__ void schedule_table(ScheduleSmem& sm, const ScheduleA
     for (int i = t; i < nbins; i += THREADS) sm.hist[i] = 0;
     __syncthreads();
 
-    // this XCD's range of logical ids (as xcd_logical_id deals them)
-    const int nblocks = BH * nb, q = nblocks >> 3, r = nblocks & 7;
-    const int lo = x * q + min(x, r), hi = lo + q + (x < r ? 1 : 0);
+    int lo, hi;   // this XCD's range of logical ids
+    schedule_range(BH * nb, x, lo, hi);
     int* out = table == 0 ? a.sched_q : a.sched_k;
     // the item of a logical id in the unsorted order and its kept-tile count
     auto item = [&](int lid, int& work) {
@@ -153,14 +222,7 @@ __device__ __forceinline__ void schedule_table(ScheduleSmem& sm, const ScheduleA
             idx = lid % nb;
         }
         const int blk = table == 0 ? nb - 1 - idx : idx;   // longest rows / first keys first
-        work = 0;
-        for (int u = 0; u < 2; ++u) {
-            const int m = 2 * blk + u;
-            if (m < M) {
-                work += table == 0 ? m - row_start[(size_t)bh * M + m] + 1
-                                   : col_end[(size_t)bh * M + m] - m + 1;
-            }
-        }
+        work = schedule_work(a, table, bh, blk);
         return bh * nb + blk;
     };
     for (int lid = lo + t; lid < hi; lid += THREADS) {

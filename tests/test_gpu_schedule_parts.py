@@ -45,3 +45,32 @@ def test_long_schedule(B, H, L, parts, seed):
             assert max(loads) <= sum(loads) / 8 + BH * 2 * M
         elif parts > 1:
             assert max(loads) <= 1.3 * sum(loads) / 8
+
+
+@pytest.mark.parametrize("B,H,L,mu,seed", [
+    (1, 16, 4096, 25.0, 91),     # nothing pruned: two whole heads per XCD
+    (2, 16, 4160, 25.0, 92),     # four, the last block ragged
+    (1, 24, 8192, -2.0, 93),     # two or three tiles per row everywhere: three whole heads
+    (1, 20, 4096, -2.0, 94),     # two and a half heads per XCD, in head order
+    (1, 3, 16384, -2.0, 95),
+])
+def test_equal_long_heads_stay_whole(B, H, L, mu, seed):
+    """Heads of equal work are not divided: parts would balance nothing, and every XCD
+    would read every head's keys and values."""
+    w = workloads.custom(f"even{seed}", B, H, L, 64, "bf16", seed, mu=(mu,))
+    print(f"case: schedule {w.describe()}", flush=True)
+    x = workloads.generate(w, with_grad=False)
+    g = {k: (v.cuda() if torch.is_tensor(v) else v) for k, v in x.items()}
+    _, _, ws = acp.forward(g["q"], g["k"], g["v"], g["log_f"], w.eps)
+    torch.cuda.synchronize()
+    pv = acp.plan_views(ws, B, H, L, 64, torch.bfloat16)
+    BH, nb = B * H, (L + 127) // 128
+    for table in ("q", "k"):
+        sched = pv["sched_" + table].cpu().numpy().astype(np.int64)
+        assert sorted(sched.tolist()) == list(range(BH * nb)), "not a permutation"
+        for lo, hi in xcd_ranges(BH * nb):
+            heads = set((sched[lo:hi] // nb).tolist())
+            if BH % 8 == 0:
+                assert len(heads) == BH // 8
+            else:
+                assert heads == set(range(lo // nb, (hi - 1) // nb + 1))

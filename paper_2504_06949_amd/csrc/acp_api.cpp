@@ -343,6 +343,8 @@ static acp_status fwd_common(const void* Q, const void* K, const void* V, const 
     sched.BH = B * H; sched.M = L / 64; sched.nb = (L + 127) / 128;
     sched.sched_q = (int*)(w + y.sched_q);
     sched.sched_k = (int*)(w + y.sched_k);
+    // (the gate producer's scan, which is over, leaves its descriptors free)
+    if (acp::bwd_groups(d, B * H * sched.nb, sched.nb).by_plan) sched.chain = (int*)(w + y.gate_agg);
     const bool direct = acp::forward_direct(d, B * H * sched.nb, sched.nb);
     if (dt == ACP_BF16 && !direct) {
         e = acp::launch_schedule(sched, (hipStream_t)stream);
@@ -477,6 +479,7 @@ acp_status fox_attn_bwd(const void* Q, const void* K, const void* V, const void*
     b.row_start = (const int*)(w + y.rs);
     b.col_end = (const int*)(w + y.ce);
     b.lse2 = (const float*)(w + y.lse2);
+    b.chain = (const int*)(w + y.gate_agg);
     b.sched_q = (const int*)(w + y.sched_q);
     b.sched_k = (const int*)(w + y.sched_k);
     b.dsum = (float*)(w + y.dsum);

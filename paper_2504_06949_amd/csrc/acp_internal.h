@@ -63,6 +63,8 @@ struct ScheduleArgs {
     int BH, M, nb;
     int* sched_q;             // query blocks (forward, dQ pass)
     int* sched_k;             // key blocks (dK/dV pass)
+    int* chain;               // if not null, gets 1 or 0: whether the launch is bound by its
+                              // longest block (kChainBound)
 };
 // Blocks per head from which heads are placed in parts.
 constexpr int kLongBlocks = 32;
@@ -107,6 +109,7 @@ struct BwdArgs {
     const int* row_start;
     const int* col_end;
     const float* lse2;
+    const int* chain;         // of the schedule, where bwd_groups goes by the plan
     const int* sched_q;       // query-block schedule (dQ pass)
     const int* sched_k;       // key-block schedule (dK/dV pass)
     float* dsum;              // Delta' from the dQ pass
@@ -174,11 +177,11 @@ struct DecodeArgs {
 // shorter when the blocks (nblocks of them, nb per head) are too few to fill the chip.
 // The price is that a CU's waves meet at one barrier per step instead of running as
 // independent workgroups, so one group stays the better form as soon as there are
-// blocks enough.  Measured, us with one group -> with G:
+// blocks enough.  Measured on heads of unequal length, us with one group -> with G:
 //   forward, d = 64 (4 workgroups per CU), G = 2: 512 blocks of nb = 32 66 -> 55, 768 of
-//     64 137 -> 116, 1024 of 32 81 -> 77; but 768 of 8 27 -> 32, 1280 of 32 92 -> 97,
-//     1344 of 56 152 -> 157.  G = 4: 205 of 41 73 -> 51 (G = 2: 57), 192 of 16 35 -> 28
-//     (29); but 512 of 32 56 (55), 768 of 64 126 (116).
+//     64 137 -> 116, 1024 of 64 170 -> 145, of 128 312 -> 254; but 768 of 8 27 -> 32, 1024 of
+//     32 107 -> 113 (unpruned), 1280 of 32 92 -> 97, 1344 of 56 152 -> 157.  G = 4: 205 of 41
+//     73 -> 51 (G = 2: 57), 256 of 128 151 (173); but 512 of 32 56 (55), 768 of 64 126 (116).
 //   forward, d = 128 (2 per CU), G = 2: 512 of 32 105 -> 82, 512 of 64 193 -> 139; but 768
 //     of 32 111 -> 111, 1024 of 32 127 -> 143.
 //   dQ, d = 64 (3 per CU), G = 3: 96 of 8 25 -> 24, 192 of 16 42 -> 35, 512 of 32 82 -> 71,
@@ -189,16 +192,28 @@ struct DecodeArgs {
 //     64 207 -> 160; but 1024 of 32 130 -> 135, 1344 of 56 233 -> 253.  (At d = 128 its
 //     LDS holds one group of 8 waves.)
 // Below 8 blocks per head the prologue and the merge outweigh the shorter chain.
-inline int fwd_groups(int d, int nblocks, int nb) {
-    if (nb < 8) return 1;
-    if (d == 128) return nblocks <= 512 ? 2 : 1;
-    if (nblocks <= 256 && nb >= 16) return 4;
-    return nblocks <= 1024 && nblocks <= 32 * nb ? 2 : 1;
+// Beyond 256 blocks the forms with one workgroup of G groups per CU (the backward's, and
+// the d = 128 forward's) run in rounds, which pays only where the longest block sets the
+// time: with equal heads of a short window, backward at d = 64, 512 blocks of 32, 33 us with
+// one group, 50 with 3, 768 of 64 45 and 73; forward at d = 128, 384 of 32 34 and 42.  There
+// both forms are launched and the schedule's `chain` says which one works (`by_plan`); an
+// empty launch costs 2 to 3 us.  (The direct forward has no schedule before it: its G = 2
+// costs equal heads of a window 640 to 1024 blocks up to 7%.)
+struct Groups {
+    int groups;
+    bool by_plan;   // that many if the launch is bound by its longest block, else one
+};
+inline Groups fwd_groups(int d, int nblocks, int nb, bool direct) {
+    if (nb < 8) return {1, false};
+    if (d == 128) return nblocks <= 512 ? Groups{2, !direct && nblocks > 256} : Groups{1, false};
+    if (!direct) return {1, false};   // (d = 64: several groups in the direct form only)
+    if (nblocks <= 256 && nb >= 16) return {4, false};
+    return {nblocks <= 1024 && nblocks <= (nblocks <= 512 ? 32 : 24) * nb ? 2 : 1, false};
 }
-inline int bwd_groups(int d, int nblocks, int nb) {
-    if (nb < 8) return 1;
-    if (d == 128) return nblocks <= 512 ? 2 : 1;
-    return nblocks <= 768 && nblocks <= 16 * nb ? 3 : 1;
+inline Groups bwd_groups(int d, int nblocks, int nb) {
+    if (nb < 8) return {1, false};
+    if (d == 128) return nblocks <= 512 ? Groups{2, nblocks > 256} : Groups{1, false};
+    return nblocks <= 768 && nblocks <= 16 * nb ? Groups{3, nblocks > 256} : Groups{1, false};
 }
 
 // Records the message that acp_last_error() returns and passes the status on.

@@ -52,7 +52,13 @@ __host__ __device__ constexpr int schedule_log_parts(int BH, int nb) {
 // 16384 tokens (d = 128) forward 1034 us in whole heads, 1161 in parts, backward 3169 and
 // 3472; 32 of 8192 549 and 590; 20 of 8192 (d = 64), each pruned to 3 tiles per row, 44 and 51.
 // So they are divided only if the heaviest XCD would carry more than this over the average.
-constexpr float kEvenLoad = 1.05f;
+constexpr float kEvenLoad = 1.06f;
+
+// Whether the longest block, not the sum of all, sets the time of a launch whose blocks are
+// all resident with one group of waves each: from the longest last row against the mean
+// over all rows, in tiles, on.  Heads of one window have a ratio of 1 to 1.5, unpruned ones
+// 2, heads of unequal length more.
+constexpr float kChainBound = 1.6f;
 
 struct ScheduleSmem {
     int sorted[kHeadsMax];                           // kept counts, largest first
@@ -143,6 +149,20 @@ __device__ __forceinline__ void schedule_table(ScheduleSmem& sm, const ScheduleA
         return rank;
     };
     static_assert(THREADS >= kPlaceMax, "a thread per part");
+    if (a.chain != nullptr && x == 0 && table == 0 && t >= THREADS - 64) {   // (the last wave)
+        int longest = 0;
+        float total = 0.f;
+        for (int h = t & 63; h < BH; h += 64) {
+            longest = max(longest, M - a.row_start[(size_t)h * M + M - 1]);
+            total += (float)kept[h];
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            longest = max(longest, __shfl_xor(longest, off));
+            total += __shfl_xor(total, off);
+        }
+        if ((t & 63) == 0) *a.chain = (float)longest * (float)BH * (float)M >= kChainBound * total ? 1 : 0;
+    }
     if (BH <= kHeadsMax && (BH % 8 == 0 || schedule_log_parts(BH, nb) > 0) && t < kPlaceMax)
         sm.kept[t] = t < BH ? (int)min(max(kept[t], 0ll), 1ll << 22) : -1;
     __syncthreads();
@@ -261,6 +281,12 @@ __device__ __forceinline__ void schedule_table(ScheduleSmem& sm, const ScheduleA
         out[atomicAdd(&sm.hist[work], 1)] = it;
     }
 }
+
+// In the kernels whose workgroups hold several groups of waves (fwd_groups, bwd_groups): a
+// block of up to this many tiles is taken by one group, without the merge: with 2 to 3 tiles
+// per row, d = 64, 128 blocks backward 28 -> 24 us, forward 20.1 -> 20.0, 256 34 -> 30 and 25 ->
+// 24; 9 tiles instead of 6 are no better (2 groups 21.3 us, one 22.4).
+constexpr int kSoloTiles = 6;
 
 // Calls whose blocks are all resident at once need no table in the forward
 // (forward_direct): workgroup i takes block nb - 1 - i / BH of head i % BH + i / BH (mod

@@ -23,6 +23,7 @@
 
 #include "acp_device.h"
 #include "acp_internal.h"
+#include "acp_schedule.h"
 
 namespace acp {
 
@@ -45,20 +46,22 @@ struct alignas(1024) DqTiles {
     float kc[2][64];               // c_j (diagonal tiles)
 };
 
-template <int D, int G>
+// kByPlan: one of two launches, of which the schedule's `chain` picks one.
+template <int D, int G, bool kByPlan>
 __global__ __launch_bounds__(kBwdThreads * G) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
 void dq_bf16_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
     const __bf16* __restrict__ O, const __bf16* __restrict__ dO, const float* __restrict__ cg,
     const int* __restrict__ row_start, const float* __restrict__ lse2,
     float* __restrict__ dsum, __bf16* __restrict__ dQ, float* __restrict__ rowsum,
-    const int* __restrict__ sched, int L, int M, int nqb, int nblocks, float kscale,
-    float qscale) {
+    const int* __restrict__ sched, const int* __restrict__ chain, int L, int M, int nqb,
+    int nblocks, float kscale, float qscale) {
     constexpr int NDS = D / 32;
     constexpr int NDT = D / 16;
     __shared__ DqTiles<D> smem[G];
 
     const int item = sched[xcd_logical_id(blockIdx.x, nblocks)];   // bh * nqb + query block
+    if (kByPlan && (*chain != 0) != (G > 1)) return;
     const int bh = item / nqb;
     const int qb = item % nqb;
     // wave w of its key group: thread tid of the group's 256
@@ -75,6 +78,10 @@ void dq_bf16_kernel(
     const size_t head = (size_t)bh * L;
     const int n_lo = row_start[(size_t)bh * M + m0];
     const int n_hi = min(m0 + 1, M - 1);
+    // a short block is one group's alone (the others would cost it the merge)
+    const bool solo = G == 1 || n_hi - n_lo < kSoloTiles;
+    if (G > 1 && solo && grp > 0) return;
+    const int stride = solo ? 1 : G;
     const int w_lo = wave_on ? row_start[(size_t)bh * M + mw] : (1 << 30);
     // R of the workgroup's two query blocks and of this wave's
     const float rb0 = cg[head + q0];
@@ -275,7 +282,7 @@ void dq_bf16_kernel(
     wait_vmcnt0();
     __syncthreads();
     float4 cnext = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (n_lo + grp + G <= n_hi) cnext = issue(n_lo + grp + G, 1);
+    if (n_lo + grp + stride <= n_hi) cnext = issue(n_lo + grp + stride, 1);
     int buf = 0;
     if constexpr (D == 64) {
     auto step = [&](auto mask_tag, int n) __attribute__((always_inline)) {
@@ -291,23 +298,23 @@ void dq_bf16_kernel(
                 phase_c(rc, y);
             }
         }
-        if (n + G <= n_hi) put_kb(cnext, buf ^ 1);
-        // tile n + G has landed and every wave's reads of tile n are complete
+        if (n + stride <= n_hi) put_kb(cnext, buf ^ 1);
+        // tile n + stride has landed and every wave's reads of tile n are complete
         wait_vmcnt0_lgkmcnt0();
         __syncthreads();
-        const bool more = n + 2 * G <= n_hi;
+        const bool more = n + 2 * stride <= n_hi;
         if (more && tid < 16)
-            cnext = *reinterpret_cast<const float4*>(cg + head + 64 * (n + 2 * G) + 4 * tid);
-        if (more) dma.issue(sm.k[buf], K + (head + (size_t)64 * (n + 2 * G)) * D, w);
-        if (more) dma.issue(sm.v[buf], V + (head + (size_t)64 * (n + 2 * G)) * D, w);
+            cnext = *reinterpret_cast<const float4*>(cg + head + 64 * (n + 2 * stride) + 4 * tid);
+        if (more) dma.issue(sm.k[buf], K + (head + (size_t)64 * (n + 2 * stride)) * D, w);
+        if (more) dma.issue(sm.v[buf], V + (head + (size_t)64 * (n + 2 * stride)) * D, w);
         buf ^= 1;
     };
     // The diagonal tiles (m0 for waves 0-1, m0 + 1 = n_hi for waves 2-3) are the
     // last two; a step that holds one goes through the masking variant.
     const int n_mask = max(n_lo, n_hi - 1);
     int n = n_lo;   // the first group's tile
-    for (; n + G - 1 < n_mask; n += G) step(std::false_type{}, n + grp);
-    for (; n <= n_hi; n += G) step(std::true_type{}, n + grp);
+    for (; n + stride - 1 < n_mask; n += stride) step(std::false_type{}, n + grp);
+    for (; n <= n_hi; n += stride) step(std::true_type{}, n + grp);
     } else {
     // d = 128: phase A is split in two, S^T with the key rows and dP^T with the
     // value rows, each read just before its MFMAs, so that no more than one
@@ -400,21 +407,21 @@ void dq_bf16_kernel(
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (n + G <= n_hi) put_kb(cnext, buf ^ 1);
-        // tile n + G has landed and every wave's reads of tile n are complete
+        if (n + stride <= n_hi) put_kb(cnext, buf ^ 1);
+        // tile n + stride has landed and every wave's reads of tile n are complete
         wait_vmcnt0_lgkmcnt0();
         __syncthreads();
-        const bool more = n + 2 * G <= n_hi;
+        const bool more = n + 2 * stride <= n_hi;
         if (more && tid < 16)
-            cnext = *reinterpret_cast<const float4*>(cg + head + 64 * (n + 2 * G) + 4 * tid);
-        if (more) dma.issue(sm.k[buf], K + (head + (size_t)64 * (n + 2 * G)) * D, w);
-        if (more) dma.issue(sm.v[buf], V + (head + (size_t)64 * (n + 2 * G)) * D, w);
+            cnext = *reinterpret_cast<const float4*>(cg + head + 64 * (n + 2 * stride) + 4 * tid);
+        if (more) dma.issue(sm.k[buf], K + (head + (size_t)64 * (n + 2 * stride)) * D, w);
+        if (more) dma.issue(sm.v[buf], V + (head + (size_t)64 * (n + 2 * stride)) * D, w);
         buf ^= 1;
     };
     const int n_mask = max(n_lo, n_hi - 1);
     int n = n_lo;   // the first group's tile
-    for (; n + G - 1 < n_mask; n += G) step(std::false_type{}, n + grp);
-    for (; n <= n_hi; n += G) step(std::true_type{}, n + grp);
+    for (; n + stride - 1 < n_mask; n += stride) step(std::false_type{}, n + grp);
+    for (; n <= n_hi; n += stride) step(std::true_type{}, n + grp);
     }
 
     if constexpr (G > 1) {
@@ -435,16 +442,18 @@ void dq_bf16_kernel(
                 if (g == 0) (&sm.kb[0][0][0])[32 * w + 16 * qt + r16] = sds[qt];
             }
         }
-        lds_barrier();
-        if (grp > 0) return;
+        if (!solo) {
+            lds_barrier();
+            if (grp > 0) return;
 #pragma unroll
-        for (int j = 1; j < G; ++j) {
-            const f32x4* so = reinterpret_cast<const f32x4*>(&smem[j].k[0][0]);
+            for (int j = 1; j < G; ++j) {
+                const f32x4* so = reinterpret_cast<const f32x4*>(&smem[j].k[0][0]);
 #pragma unroll
-            for (int qt = 0; qt < 2; ++qt) {
+                for (int qt = 0; qt < 2; ++qt) {
 #pragma unroll
-                for (int dt = 0; dt < NDT; ++dt) acc[qt][dt] += so[((w * 2 + qt) * NDT + dt) * 64 + lane];
-                sds[qt] += (&smem[j].kb[0][0][0])[32 * w + 16 * qt + r16];
+                    for (int dt = 0; dt < NDT; ++dt) acc[qt][dt] += so[((w * 2 + qt) * NDT + dt) * 64 + lane];
+                    sds[qt] += (&smem[j].kb[0][0][0])[32 * w + 16 * qt + r16];
+                }
             }
         }
     }
@@ -521,15 +530,16 @@ struct alignas(1024) DkvSmem {
     float kc[128];                 // c_j of the workgroup's keys (diagonal tiles)
 };
 
-template <int D, int G>
+template <int D, int G, bool kByPlan>
 __global__ __launch_bounds__(64 * DkvShape<D>::NW * G) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
 void dkdv_bf16_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
     const __bf16* __restrict__ dO, const float* __restrict__ cg,
     const int* __restrict__ col_end, const float* __restrict__ lse2,
     const float* __restrict__ dsum, __bf16* __restrict__ dK, __bf16* __restrict__ dV,
-    float* __restrict__ colsum, const int* __restrict__ sched, int L, int M, int nkb,
-    int nblocks, float kscale, float qscale) {
+    float* __restrict__ colsum, const int* __restrict__ sched,
+    const int* __restrict__ chain, int L, int M, int nkb, int nblocks, float kscale,
+    float qscale) {
     constexpr int NDS = D / 32;
     constexpr int NDT = D / 16;
     constexpr int QSPLIT = DkvShape<D>::QSPLIT, NW = DkvShape<D>::NW;
@@ -538,6 +548,7 @@ void dkdv_bf16_kernel(
     __shared__ DkvSmem<D, G> sg;
 
     const int item = sched[xcd_logical_id(blockIdx.x, nblocks)];   // bh * nkb + key block
+    if (kByPlan && (*chain != 0) != (G > 1)) return;
     const int bh = item / nkb;
     const int kb = item % nkb;
     // wave w of its query group: thread tid of the group's 64 NW
@@ -557,6 +568,9 @@ void dkdv_bf16_kernel(
     const size_t head = (size_t)bh * L;
     const int m_lo = n0;
     const int m_hi = col_end[(size_t)bh * M + min(n0 + 1, M - 1)];
+    const bool solo = G == 1 || m_hi - m_lo < kSoloTiles;   // (as in the dQ pass)
+    if (G > 1 && solo && grp > 0) return;
+    const int stride = solo ? 1 : G;
     const int w_hi = wave_on ? col_end[(size_t)bh * M + nw] : -1;
     const float kinv = 1.0f / kscale;
     // R of the workgroup's two key blocks (the gate at each block's last key; the
@@ -783,7 +797,7 @@ void dkdv_bf16_kernel(
     wait_vmcnt0();
     __syncthreads();
     float3 rnext = make_float3(0.f, 0.f, 0.f);
-    if (m_lo + grp + G <= m_hi) rnext = issue(m_lo + grp + G, 1);
+    if (m_lo + grp + stride <= m_hi) rnext = issue(m_lo + grp + stride, 1);
     int buf = 0;
     auto step = [&](auto mask_tag, int m) __attribute__((always_inline)) {
         const bool act = m >= nw && m <= w_hi;
@@ -811,25 +825,25 @@ void dkdv_bf16_kernel(
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (m + G <= m_hi) put_rows(rnext, buf ^ 1);
-        // tile m + G has landed and every wave's reads of tile m are complete
+        if (m + stride <= m_hi) put_rows(rnext, buf ^ 1);
+        // tile m + stride has landed and every wave's reads of tile m are complete
         wait_vmcnt0_lgkmcnt0();
         __syncthreads();
-        const bool more = m + 2 * G <= m_hi;
+        const bool more = m + 2 * stride <= m_hi;
         if (more && tid < 64) {
-            const size_t row = head + 64 * (m + 2 * G) + tid;
+            const size_t row = head + 64 * (m + 2 * stride) + tid;
             rnext = make_float3(cg[row], lse2[row], dsum[row]);
         }
-        if (more) dma.issue(sm.q[buf], Q + (head + (size_t)64 * (m + 2 * G)) * D, w);
-        if (more) dma.issue(sm.o[buf], dO + (head + (size_t)64 * (m + 2 * G)) * D, w);
+        if (more) dma.issue(sm.q[buf], Q + (head + (size_t)64 * (m + 2 * stride)) * D, w);
+        if (more) dma.issue(sm.o[buf], dO + (head + (size_t)64 * (m + 2 * stride)) * D, w);
         buf ^= 1;
     };
     // The first block's waves meet their diagonal tile at m_lo, the second
     // block's at m_lo + 1; the steps that hold them go through the masking variant.
     const int m_diag = min(m_lo + 1, m_hi);
     int m = m_lo;   // the first group's tile
-    for (; m <= m_diag; m += G) step(std::true_type{}, m + grp);
-    for (; m <= m_hi; m += G) step(std::false_type{}, m + grp);
+    for (; m <= m_diag; m += stride) step(std::true_type{}, m + grp);
+    for (; m <= m_hi; m += stride) step(std::false_type{}, m + grp);
 
     if constexpr (G > 1) {
         // The other groups' sums go to the first through their tiles' LDS, no longer
@@ -862,14 +876,16 @@ void dkdv_bf16_kernel(
                 }
             }
         };
-        hand_over(dk);
-        lds_barrier();
-        hand_over(dv);
-        if (grp > 0) return;
+        if (!solo) {
+            hand_over(dk);
+            lds_barrier();
+            hand_over(dv);
+            if (grp > 0) return;
 #pragma unroll
-        for (int j = 1; j < G; ++j)
+            for (int j = 1; j < G; ++j)
 #pragma unroll
-            for (int kt = 0; kt < 2; ++kt) csum[kt] += (&sg.grp[j].la[0][0][0])[32 * kg + 16 * kt + r16];
+                for (int kt = 0; kt < 2; ++kt) csum[kt] += (&sg.grp[j].la[0][0][0])[32 * kg + 16 * kt + r16];
+        }
     }
 
     if constexpr (QSPLIT == 2) {
@@ -936,44 +952,66 @@ void dkdv_bf16_kernel(
 }
 
 // ---------------------------------------------------------------------------
-template <int D, int G>
+template <int D, int G, bool kByPlan = false>
 static void dq_t(const BwdArgs& a, hipStream_t s) {
     const int nqb = (a.L + kBwdRows - 1) / kBwdRows, nblocks = a.B * a.H * nqb;
-    hipLaunchKernelGGL((dq_bf16_kernel<D, G>), dim3(nblocks), dim3(kBwdThreads * G), 0, s,
+    hipLaunchKernelGGL((dq_bf16_kernel<D, G, kByPlan>), dim3(nblocks), dim3(kBwdThreads * G), 0, s,
                        (const __bf16*)a.Q, (const __bf16*)a.K, (const __bf16*)a.V,
                        (const __bf16*)a.O, (const __bf16*)a.dO, a.c, a.row_start, a.lse2,
-                       a.dsum, (__bf16*)a.dQ, a.rowsum, a.sched_q, a.L, a.L / 64, nqb, nblocks,
-                       kLog2e / sqrtf((float)D), 1.0f / sqrtf((float)D));
+                       a.dsum, (__bf16*)a.dQ, a.rowsum, a.sched_q, a.chain, a.L, a.L / 64, nqb,
+                       nblocks, kLog2e / sqrtf((float)D), 1.0f / sqrtf((float)D));
 }
 
+template <int D, int G, bool kByPlan = false>
+static void dkdv_t(const BwdArgs& a, hipStream_t s) {
+    const int nkb = (a.L + kBwdRows - 1) / kBwdRows, nblocks = a.B * a.H * nkb;
+    hipLaunchKernelGGL((dkdv_bf16_kernel<D, G, kByPlan>), dim3(nblocks),
+                       dim3(64 * DkvShape<D>::NW * G), 0, s, (const __bf16*)a.Q, (const __bf16*)a.K,
+                       (const __bf16*)a.V, (const __bf16*)a.dO, a.c, a.col_end, a.lse2,
+                       a.dsum, (__bf16*)a.dK, (__bf16*)a.dV, a.colsum, a.sched_k, a.chain, a.L,
+                       a.L / 64, nkb, nblocks, kLog2e / sqrtf((float)D), 1.0f / sqrtf((float)D));
+}
+
+// One group of waves per block or several, by the number of blocks or, in two launches, by
+// the plan (bwd_groups)
 hipError_t launch_dq_bf16(const BwdArgs& a, hipStream_t s) {
     const int nb = (a.L + kBwdRows - 1) / kBwdRows;
-    const int G = bwd_groups(a.d, a.B * a.H * nb, nb);
+    const Groups g = bwd_groups(a.d, a.B * a.H * nb, nb);
     if (a.d == 64) {
-        if (G == 3) dq_t<64, 3>(a, s);
-        else dq_t<64, 1>(a, s);
+        if (g.groups == 1) {
+            dq_t<64, 1>(a, s);
+        } else if (g.by_plan) {
+            dq_t<64, 1, true>(a, s);
+            dq_t<64, 3, true>(a, s);
+        } else {
+            dq_t<64, 3>(a, s);
+        }
     } else {
-        if (G == 2) dq_t<128, 2>(a, s);
-        else dq_t<128, 1>(a, s);
+        if (g.groups == 1) {
+            dq_t<128, 1>(a, s);
+        } else if (g.by_plan) {
+            dq_t<128, 1, true>(a, s);
+            dq_t<128, 2, true>(a, s);
+        } else {
+            dq_t<128, 2>(a, s);
+        }
     }
     return hipGetLastError();
 }
 
-template <int D, int G>
-static void dkdv_t(const BwdArgs& a, hipStream_t s) {
-    const int nkb = (a.L + kBwdRows - 1) / kBwdRows, nblocks = a.B * a.H * nkb;
-    hipLaunchKernelGGL((dkdv_bf16_kernel<D, G>), dim3(nblocks), dim3(64 * DkvShape<D>::NW * G), 0, s,
-                       (const __bf16*)a.Q, (const __bf16*)a.K, (const __bf16*)a.V,
-                       (const __bf16*)a.dO, a.c, a.col_end, a.lse2, a.dsum, (__bf16*)a.dK,
-                       (__bf16*)a.dV, a.colsum, a.sched_k, a.L, a.L / 64, nkb, nblocks,
-                       kLog2e / sqrtf((float)D), 1.0f / sqrtf((float)D));
-}
-
 hipError_t launch_dkdv_bf16(const BwdArgs& a, hipStream_t s) {
     const int nb = (a.L + kBwdRows - 1) / kBwdRows;
-    if (a.d == 128) dkdv_t<128, 1>(a, s);
-    else if (bwd_groups(64, a.B * a.H * nb, nb) == 3) dkdv_t<64, 3>(a, s);
-    else dkdv_t<64, 1>(a, s);
+    const Groups g = bwd_groups(a.d, a.B * a.H * nb, nb);
+    if (a.d == 128) {   // (its LDS holds one group of 8 waves)
+        dkdv_t<128, 1>(a, s);
+    } else if (g.groups == 1) {
+        dkdv_t<64, 1>(a, s);
+    } else if (g.by_plan) {
+        dkdv_t<64, 1, true>(a, s);
+        dkdv_t<64, 3, true>(a, s);
+    } else {
+        dkdv_t<64, 3>(a, s);
+    }
     return hipGetLastError();
 }
 

@@ -43,6 +43,7 @@ namespace acp {
 constexpr int kFwdThreads = 256;
 constexpr int kFwdRows = 128;
 constexpr double kUFixedMax = 32.0;
+constexpr int kTableGroups = 16;   // workgroups that fill the schedule tables: 8 XCDs, 2 tables
 
 // ---------------------------------------------------------------------------
 // bf16 path: v_mfma_f32_16x16x32_bf16, fp32 accumulation.
@@ -102,6 +103,10 @@ __device__ __forceinline__ void fwd_bf16_body(
     const size_t head = (size_t)bh * L;
     const int n_lo = row_start[(size_t)bh * M + m0];
     const int n_hi = min(m0 + 1, M - 1);
+    // a short block is one group's alone (the others would cost it the merge)
+    const bool solo = G == 1 || n_hi - n_lo < kSoloTiles;
+    if (G > 1 && solo && grp > 0) return;
+    const int stride = solo ? 1 : G;
     const int w_lo = wave_on ? row_start[(size_t)bh * M + mw] : (1 << 30);
     // R of the workgroup's two query blocks (the second repeats the first when
     // the sequence ends after 64 rows) and of this wave's block
@@ -323,7 +328,7 @@ __device__ __forceinline__ void fwd_bf16_body(
     wait_vmcnt0();
     __syncthreads();
     float4 cnext = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (n_lo + grp + G <= n_hi) cnext = issue(n_lo + grp + G, 1);
+    if (n_lo + grp + stride <= n_hi) cnext = issue(n_lo + grp + stride, 1);
     int buf = 0;
     auto step = [&](auto mask_tag, int n) __attribute__((always_inline)) {
         const bool act = n >= w_lo && n <= mw;
@@ -342,23 +347,23 @@ __device__ __forceinline__ void fwd_bf16_body(
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (n + G <= n_hi) put_kb(cnext, buf ^ 1);
-        // tile n + G has landed and every wave's reads of tile n are complete
+        if (n + stride <= n_hi) put_kb(cnext, buf ^ 1);
+        // tile n + stride has landed and every wave's reads of tile n are complete
         wait_vmcnt0_lgkmcnt0();
         __syncthreads();
-        const bool more = n + 2 * G <= n_hi;
+        const bool more = n + 2 * stride <= n_hi;
         if (more && tid < 16)
-            cnext = *reinterpret_cast<const float4*>(cg + head + 64 * (n + 2 * G) + 4 * tid);
-        if (more) dma.issue(sm.k[buf], K + (head + (size_t)64 * (n + 2 * G)) * D, w);
-        if (more) dma.issue(sm.v[buf], V + (head + (size_t)64 * (n + 2 * G)) * D, w);
+            cnext = *reinterpret_cast<const float4*>(cg + head + 64 * (n + 2 * stride) + 4 * tid);
+        if (more) dma.issue(sm.k[buf], K + (head + (size_t)64 * (n + 2 * stride)) * D, w);
+        if (more) dma.issue(sm.v[buf], V + (head + (size_t)64 * (n + 2 * stride)) * D, w);
         buf ^= 1;
     };
     // The diagonal tiles (m0 for waves 0-1, m0 + 1 for waves 2-3) are the last
     // two; a step that holds one goes through the masking variant.
     const int n_mask = max(n_lo, n_hi - 1);
     int n = n_lo;   // the first group's tile
-    for (; n + G - 1 < n_mask; n += G) step(std::false_type{}, n + grp);
-    for (; n <= n_hi; n += G) step(std::true_type{}, n + grp);
+    for (; n + stride - 1 < n_mask; n += stride) step(std::false_type{}, n + grp);
+    for (; n <= n_hi; n += stride) step(std::true_type{}, n + grp);
 
     if constexpr (G > 1) {
         // The other groups hand their partial sums to the first through their tiles'
@@ -380,8 +385,10 @@ __device__ __forceinline__ void fwd_bf16_body(
                 }
             }
         }
-        lds_barrier();
-        if (grp > 0) return;
+        if (!solo) {
+            lds_barrier();
+            if (grp > 0) return;
+        }
     }
     if (!wave_on) return;
 #pragma unroll
@@ -389,7 +396,7 @@ __device__ __forceinline__ void fwd_bf16_body(
         float lt = lrun[qt];
         lt += __shfl_xor(lt, 16);
         lt += __shfl_xor(lt, 32);
-        if constexpr (G > 1) {
+        if (G > 1 && !solo) {
 #pragma unroll
             for (int j = 1; j < G; ++j) {
                 const f32x4* so = reinterpret_cast<const f32x4*>(&smem.grp[j].k[0][0]);
@@ -439,10 +446,11 @@ __device__ __forceinline__ void fwd_bf16_body(
 
 // One launch for both variants: the head's bound picks the body (uniform over
 // the workgroup), and the two bodies share the workgroup's LDS.
-// kDirect: without the schedule tables, which 16 spare workgroups then fill
-// (forward_direct); a kernel of its own, so that the tables' code does not weigh on the
+// kDirect: without the schedule tables, which 16 more workgroups fill, the first ones, so
+// that what may have to wait for a slot are the shortest blocks (forward_direct); a kernel of its own, so that the tables' code does not weigh on the
 // registers of the other (d = 128: 215 VGPRs instead of 209, 0.8% slower).
-template <int D, int G, bool kDirect>
+// kByPlan: one of two launches, of which the schedule's `chain` picks one.
+template <int D, int G, bool kDirect, bool kByPlan>
 __global__ __launch_bounds__(kFwdThreads * G) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
 void fwd_bf16_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
@@ -453,16 +461,18 @@ void fwd_bf16_kernel(
     __shared__ FwdSmem<D, G> sm;
     static_assert(sizeof(sm) >= sizeof(ScheduleSmem), "the tables' scratch");
     int item;   // bh * nqb + query block
+    static_assert(!(kDirect && kByPlan), "a direct launch fills `chain` itself");
     if constexpr (kDirect) {
-        if ((int)blockIdx.x >= nblocks) {
-            const int e = blockIdx.x - nblocks;
-            schedule_table<kFwdThreads * G>(reinterpret_cast<ScheduleSmem&>(sm), sched, e & 7, e >> 3);
+        const int i = (int)blockIdx.x - kTableGroups;
+        if (i < 0) {
+            schedule_table<kFwdThreads * G>(reinterpret_cast<ScheduleSmem&>(sm), sched, blockIdx.x & 7, blockIdx.x >> 3);
             return;
         }
-        item = direct_item(blockIdx.x, sched.BH, nqb);
+        item = direct_item(i, sched.BH, nqb);
     } else {
         item = sched.sched_q[xcd_logical_id(blockIdx.x, nblocks)];
     }
+    if (kByPlan && (*sched.chain != 0) != (G > 1)) return;
     const int bh = item / nqb;
     const double u_head = bound_u[bh];
     if (u_head <= kUFixedMax)
@@ -474,14 +484,14 @@ void fwd_bf16_kernel(
 }
 
 // ---------------------------------------------------------------------------
-template <int D, int G, bool kDirect>
+template <int D, int G, bool kDirect, bool kByPlan = false>
 static void launch_fwd_bf16(const FwdArgs& a, int M, float kscale, hipStream_t s) {
     const int BH = a.B * a.H;
     const int nqb = (a.L + kFwdRows - 1) / kFwdRows;
     const int nblocks = BH * nqb;
-    const int grid = nblocks + (kDirect ? 16 : 0);
-    hipLaunchKernelGGL((fwd_bf16_kernel<D, G, kDirect>), dim3(grid), dim3(kFwdThreads * G), 0, s,
-                       (const __bf16*)a.Q, (const __bf16*)a.K, (const __bf16*)a.V, a.c,
+    const int grid = nblocks + (kDirect ? kTableGroups : 0);
+    hipLaunchKernelGGL((fwd_bf16_kernel<D, G, kDirect, kByPlan>), dim3(grid), dim3(kFwdThreads * G),
+                       0, s, (const __bf16*)a.Q, (const __bf16*)a.K, (const __bf16*)a.V, a.c,
                        a.row_start, a.u, a.sched, (__bf16*)a.O, a.lse, a.lse2, a.L, M, nqb,
                        nblocks, kscale);
 }
@@ -493,19 +503,23 @@ hipError_t launch_fwd(const FwdArgs& a, hipStream_t s) {
     hipError_t e;
     if (a.bf16) {
         const int nb = (a.L + kFwdRows - 1) / kFwdRows;
-        const int G = fwd_groups(a.d, a.B * a.H * nb, nb);
-        if (a.d == 64) {
-            // (several groups only up to 1024 blocks, which are always direct)
-            if (G == 4) launch_fwd_bf16<64, 4, true>(a, M, kscale, s);
-            else if (G == 2) launch_fwd_bf16<64, 2, true>(a, M, kscale, s);
-            else if (a.direct) launch_fwd_bf16<64, 1, true>(a, M, kscale, s);
-            else launch_fwd_bf16<64, 1, false>(a, M, kscale, s);
+        const Groups g = fwd_groups(a.d, a.B * a.H * nb, nb, a.direct);
+        if (a.d == 64 && a.direct) {
+            if (g.groups == 4) launch_fwd_bf16<64, 4, true>(a, M, kscale, s);
+            else if (g.groups == 2) launch_fwd_bf16<64, 2, true>(a, M, kscale, s);
+            else launch_fwd_bf16<64, 1, true>(a, M, kscale, s);
+        } else if (a.d == 64) {
+            launch_fwd_bf16<64, 1, false>(a, M, kscale, s);
         } else if (a.direct) {
-            if (G == 2) launch_fwd_bf16<128, 2, true>(a, M, kscale, s);
+            if (g.groups == 2) launch_fwd_bf16<128, 2, true>(a, M, kscale, s);
             else launch_fwd_bf16<128, 1, true>(a, M, kscale, s);
+        } else if (g.groups == 1) {
+            launch_fwd_bf16<128, 1, false>(a, M, kscale, s);
+        } else if (g.by_plan) {
+            launch_fwd_bf16<128, 1, false, true>(a, M, kscale, s);
+            launch_fwd_bf16<128, 2, false, true>(a, M, kscale, s);
         } else {
-            if (G == 2) launch_fwd_bf16<128, 2, false>(a, M, kscale, s);
-            else launch_fwd_bf16<128, 1, false>(a, M, kscale, s);
+            launch_fwd_bf16<128, 2, false>(a, M, kscale, s);
         }
         e = hipGetLastError();
     } else {

@@ -52,7 +52,11 @@ __host__ __device__ constexpr int schedule_log_parts(int BH, int nb) {
 // 16384 tokens (d = 128) forward 1034 us in whole heads, 1161 in parts, backward 3169 and
 // 3472; 32 of 8192 549 and 590; 20 of 8192 (d = 64), each pruned to 3 tiles per row, 44 and 51.
 // So they are divided only if the heaviest XCD would carry more than this over the average.
-constexpr float kEvenLoad = 1.06f;
+// 100 mixes of heads, in parts against whole: in 2 or 4 parts up to 1.06 over the average 0 to 12%
+// slower, from 1.10 on 0 to 6% faster (20 unpruned heads); in 8 parts, where every XCD reads
+// every head, up to 1.10 0 to 16% slower (14 heads of 8192 with a window, d = 128, forward 272
+// and 228 us), from 1.15 on even or up to 10% faster.
+__device__ __forceinline__ float schedule_even_load(int log_parts) { return log_parts == 3 ? 1.105f : 1.08f; }
 
 // Whether the longest block, not the sum of all, sets the time of a launch whose blocks are
 // all resident with one group of waves each: from the longest last row against the mean
@@ -96,7 +100,8 @@ __device__ __forceinline__ int schedule_work(const ScheduleArgs& a, int table, i
 // summed block by block.  sm.kept holds the counts; the answer is uniform and the same in
 // every workgroup of the table.
 template <int THREADS, typename Rank>
-__device__ __forceinline__ bool schedule_even(ScheduleSmem& sm, const ScheduleArgs& a, int table, Rank rank_of) {
+__device__ __forceinline__ bool schedule_even(ScheduleSmem& sm, const ScheduleArgs& a, int table,
+                                              float most_load, Rank rank_of) {
     const int t = threadIdx.x, lane = t & 63, BH = a.BH;
     if (BH % 8 == 0) {
         if (t < BH) sm.sorted[rank_of(t)] = sm.kept[t];
@@ -127,7 +132,7 @@ __device__ __forceinline__ bool schedule_even(ScheduleSmem& sm, const ScheduleAr
         most = max(most, sm.load[x]);
         total += (float)sm.load[x];
     }
-    return 8.f * (float)most <= kEvenLoad * total;
+    return 8.f * (float)most <= most_load * total;
 }
 
 // Table 0 (query blocks) or 1 (key blocks) for XCD x, by a workgroup of THREADS.
@@ -167,7 +172,7 @@ __device__ __forceinline__ void schedule_table(ScheduleSmem& sm, const ScheduleA
         sm.kept[t] = t < BH ? (int)min(max(kept[t], 0ll), 1ll << 22) : -1;
     __syncthreads();
     int lp = schedule_log_parts(BH, nb);                 // (0 beyond kHeadsMax heads)
-    if (lp > 0 && schedule_even<THREADS>(sm, a, table, rank_of)) lp = 0;
+    if (lp > 0 && schedule_even<THREADS>(sm, a, table, schedule_even_load(lp), rank_of)) lp = 0;
     const int parts = 1 << lp, NP = BH << lp;
     const bool deal = lp == 3 && BH <= kHeadsMax / 2;    // NP a multiple of 8, <= kPlaceMax
     const bool greedy = !deal && NP % 8 == 0 && NP <= kHeadsMax;

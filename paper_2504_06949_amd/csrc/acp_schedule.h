@@ -27,26 +27,6 @@ namespace acp {
 //   - inside each XCD range the workgroups run largest first (a counting sort
 //     on their kept-tile counts), so that the range ends on small ones.
 // Entry = bh * nb + block.  Equal counts keep no particular order.
-constexpr int kHeadsMax = 64;          // heads that are placed
-constexpr int kPlaceMax = 256;         // parts that are dealt
-
-// log2 of the parts s per head: enough that the parts make whole rounds over the
-// XCDs, 8 (then every XCD has the same share of every head) for at most 16 heads, and
-// otherwise no more than 64 parts: a head spread further costs L2 reuse.  A head's
-// kept share runs from nearly none to all, so with one or two heads per XCD the
-// heaviest XCD decides the time.  Measured, forward: 8 heads of 32768 tokens (d = 128)
-// 1956 us undivided, 1200 in 8 parts; 12 heads of 8128 tokens 198 us in bh order, 162
-// in 4 parts, 135 in 8.  (48 heads of 16384 dealt back and forth instead of to the least
-// loaded XCD: every kernel 2% slower.)  Training step at 4 x 16 heads of 8192 tokens: 1.73 ms
-// undivided, 1.77 in 2 parts, 1.83 in 4; 2 x 16 heads of 16384 (d = 128): 5.12 ms in 2
-// parts, 5.18 in 4, 5.30 in 8.
-// (33 to 63 heads that are no multiple of 8 would make more than 64 parts: in bh order.)
-__host__ __device__ constexpr int schedule_log_parts(int BH, int nb) {
-    if (nb < kLongBlocks) return 0;
-    int s = 0;
-    while (s < 3 && (BH <= 16 || ((BH << s) & 7) != 0 || (BH << (s + 1)) <= kHeadsMax)) ++s;
-    return BH << s <= kHeadsMax ? s : BH <= kHeadsMax / 2 ? 3 : 0;
-}
 
 // Heads of equal work gain nothing from parts and pay for them in L2: unpruned, 16 heads of
 // 16384 tokens (d = 128) forward 1034 us in whole heads, 1161 in parts, backward 3169 and
@@ -74,13 +54,6 @@ struct ScheduleSmem {
     int hist[2 * kMaxBlocks + 2];                    // a block's count is at most 2M <= 4096
     int wave[16];
 };
-
-// The range of logical ids of XCD x (as xcd_logical_id deals them)
-__device__ __forceinline__ void schedule_range(int nblocks, int x, int& lo, int& hi) {
-    const int q = nblocks >> 3, r = nblocks & 7;
-    lo = x * q + min(x, r);
-    hi = lo + q + (x < r ? 1 : 0);
-}
 
 // Kept tiles of a 128-row block in table 0 (queries) or 1 (keys)
 __device__ __forceinline__ int schedule_work(const ScheduleArgs& a, int table, int bh, int blk) {
@@ -174,11 +147,11 @@ __device__ __forceinline__ void schedule_table(ScheduleSmem& sm, const ScheduleA
     int lp = schedule_log_parts(BH, nb);                 // (0 beyond kHeadsMax heads)
     if (lp > 0 && schedule_even<THREADS>(sm, a, table, schedule_even_load(lp), rank_of)) lp = 0;
     const int parts = 1 << lp, NP = BH << lp;
-    const bool deal = lp == 3 && BH <= kHeadsMax / 2;    // NP a multiple of 8, <= kPlaceMax
-    const bool greedy = !deal && NP % 8 == 0 && NP <= kHeadsMax;
+    const Placing placing = schedule_placing(BH, lp);
+    const bool deal = placing == Placing::kDealt, greedy = placing == Placing::kByLoad;
     if (deal) {
         // slot (NP / 8) j + i: part j of the head of rank i
-        if (t < NP) sm.place[BH * (t & 7) + rank_of(t >> 3)] = t;
+        if (t < NP) sm.place[deal_slot(t & 7, rank_of(t >> 3), BH)] = t;
     } else if (greedy && t < 64) {
         // Wave 0 alone.  Lane j of 0-7 holds XCD j as the key load << 3 | j; each step
         // the key that equals the minimum over the 8 lanes (the least loaded XCD with
@@ -211,10 +184,10 @@ __device__ __forceinline__ void schedule_table(ScheduleSmem& sm, const ScheduleA
         }
     }
     if (lp > 0 && (deal || greedy)) {
-        // first logical id of slot t: part j has nb >> lp blocks, and one more below
-        // nb's remainder
+        // first logical id of slot t: t parts of nb >> lp blocks, and one more for those
+        // before it that have the extra block
         __syncthreads();
-        const bool more = t < NP && (sm.place[t] & (parts - 1)) < (nb & (parts - 1));
+        const bool more = t < NP && part_blocks(sm.place[t] & (parts - 1), lp, nb) > (nb >> lp);
         const unsigned long long bal = __ballot(more);
         if (t < kPlaceMax && (t & 63) == 0) sm.more[t >> 6] = __popcll(bal);
         __syncthreads();
@@ -235,12 +208,9 @@ __device__ __forceinline__ void schedule_table(ScheduleSmem& sm, const ScheduleA
     auto item = [&](int lid, int& work) {
         int bh, idx;
         if (lp > 0 && (deal || greedy)) {
-            int slot = 0;   // the last slot that starts at or before lid
-#pragma unroll
-            for (int step = kPlaceMax / 2; step >= 1; step >>= 1)
-                if (slot + step < NP && sm.first[slot + step] <= lid) slot += step;
+            const int slot = slot_of(sm.first, NP, lid);
             bh = sm.place[slot] >> lp;
-            idx = (sm.place[slot] & (parts - 1)) + ((lid - sm.first[slot]) << lp);
+            idx = part_index(sm.place[slot], lp, lid - sm.first[slot]);
         } else {
             const int slot = lid / nb;
             bh = deal || greedy ? sm.place[slot] : slot;
@@ -292,18 +262,5 @@ __device__ __forceinline__ void schedule_table(ScheduleSmem& sm, const ScheduleA
 // per row, d = 64, 128 blocks backward 28 -> 24 us, forward 20.1 -> 20.0, 256 34 -> 30 and 25 ->
 // 24; 9 tiles instead of 6 are no better (2 groups 21.3 us, one 22.4).
 constexpr int kSoloTiles = 6;
-
-// Calls whose blocks are all resident at once need no table in the forward
-// (forward_direct): workgroup i takes block nb - 1 - i / BH of head i % BH + i / BH (mod
-// BH), so that every head's longest blocks start first and its blocks are spread over
-// the XCDs (workgroup i runs on XCD i % 8).  The tables, part of the plan and the
-// backward's order, are then filled by spare workgroups of the forward's own launch
-// instead of a kernel between stage 1 and it.
-__device__ __forceinline__ int direct_item(int i, int BH, int nb) {
-    const int blk = i / BH;
-    int bh = i - blk * BH + blk % BH;
-    bh -= bh >= BH ? BH : 0;
-    return bh * nb + nb - 1 - blk;
-}
 
 }  // namespace acp

@@ -4,8 +4,9 @@
 // bfloat16 kernels (fox_fwd.hip, fox_bwd_mfma.hip).
 //
 // What bounds them: the matrix cores at 154 TFLOP/s (a large float32 torch
-// product on the same card); each 16 x 16 tile of logits costs 32 d cycles of MFMA
-// against about 40 of exp, so nothing else needs hiding but memory latency.
+// product on the same card); each product of a 16 x 16 tile costs 8 d cycles of MFMA, so
+// a tile 16 d in the forward, 24 d in the dQ and 32 d in the dK/dV pass, against about 40
+// of exp, and nothing else needs hiding but memory latency.
 //
 // Split: a workgroup owns 16 T rows (queries in the forward and the dQ pass, keys
 // in the dK/dV pass) and its 4 waves share out the other operand in 16-row

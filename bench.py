@@ -88,7 +88,7 @@ def frac_at_step_clock(w, pk: dict, executed_tflops: float):
 
 
 # device headers that every kernel file includes: a change there changes the kernels
-SHARED_HEADERS = ("acp_device.h", "acp_internal.h")
+SHARED_HEADERS = ("acp_device.h", "acp_internal.h", "acp_rules.h", "acp_schedule.h")
 
 
 def source_digest(src: str):

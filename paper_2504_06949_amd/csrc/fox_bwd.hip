@@ -25,12 +25,15 @@ namespace acp {
 
 // ---------------------------------------------------------------------------
 // dlog f_l = sum_{i >= l} (rowsum_i - colsum_i), accumulated in float64.  Each
-// thread owns a contiguous run of whole float4s (kept in registers up to kRunHeld
-// values, else read again in batches of that many, from the end); one round through
-// LDS carries the waves' totals for the suffix sums.
+// thread owns a contiguous run of whole float4s, kept in registers up to kHeld values,
+// else read again in batches of that many, from the end; one round through LDS carries
+// the waves' totals for the suffix sums.  kHeld = 4 is a whole run up to 4096 positions, and
+// two workgroups then fit a CU (kRunHeld takes 84
+// VGPRs): 4096 heads of 64 positions 28 -> 14 us, 96 of 4096 6.7 -> 6.5.
 // ---------------------------------------------------------------------------
 constexpr int kScanThreads = kPlanThreads;
 
+template <int kHeld>
 __global__ __launch_bounds__(kScanThreads) void dlogf_kernel(const float* __restrict__ rowsum,
                                                              const float* __restrict__ colsum,
                                                              float* __restrict__ dlog_f, int L) {
@@ -42,20 +45,20 @@ __global__ __launch_bounds__(kScanThreads) void dlogf_kernel(const float* __rest
     const int beg = min(t * per, L), n = min(beg + per, L) - beg;   // multiples of 4
     const float* rs = rowsum + head + beg;
     const float* cs = colsum + head + beg;
-    double dv[kRunHeld];
+    double dv[kHeld];
     auto load = [&](int b) __attribute__((always_inline)) {
-        float r[kRunHeld], c[kRunHeld];
+        float r[kHeld], c[kHeld];
         load_run(rs, b, n, true, r);
         load_run(cs, b, n, true, c);
 #pragma unroll
-        for (int i = 0; i < kRunHeld; ++i) dv[i] = (double)r[i] - (double)c[i];
+        for (int i = 0; i < kHeld; ++i) dv[i] = (double)r[i] - (double)c[i];
     };
     double local = 0.0;
-    const int last = n > 0 ? (n - 1) / kRunHeld * kRunHeld : 0;   // the run's last batch
-    for (int b = 0; b <= last; b += kRunHeld) {
+    const int last = n > 0 ? (n - 1) / kHeld * kHeld : 0;   // the run's last batch
+    for (int b = 0; b <= last; b += kHeld) {
         load(b);
 #pragma unroll
-        for (int i = 0; i < kRunHeld; ++i) local += dv[i];
+        for (int i = 0; i < kHeld; ++i) local += dv[i];
     }
     // inclusive suffix sums over the lanes of the wave: within each row of 16 by
     // zero-filled shifts toward lower lanes, then the totals of the later rows
@@ -79,10 +82,10 @@ __global__ __launch_bounds__(kScanThreads) void dlogf_kernel(const float* __rest
         after = readlane_f64(row16_reduce(v, [](double x, double y) { return x + y; }), 0);
     }
     double run = after + (suf - local);   // sum over the threads after this one
-    for (int b = last; b >= 0; b -= kRunHeld) {
+    for (int b = last; b >= 0; b -= kHeld) {
         if (b != last) load(b);   // (the last batch is still in registers)
 #pragma unroll
-        for (int i = kRunHeld - 4; i >= 0; i -= 4) {
+        for (int i = kHeld - 4; i >= 0; i -= 4) {
             if (b + i < n) {
                 float4 o;
                 run += dv[i + 3]; o.w = (float)run;
@@ -109,8 +112,8 @@ hipError_t launch_bwd(const BwdArgs& a, hipStream_t s) {
     trace_end(ACP_K_DKDV, s);
 
     trace_begin(ACP_K_DLOGF, s);
-    hipLaunchKernelGGL(dlogf_kernel, dim3(a.B * a.H), dim3(kScanThreads), 0, s, a.rowsum, a.colsum,
-                       a.dlog_f, a.L);
+    hipLaunchKernelGGL((a.L <= 4 * kScanThreads ? dlogf_kernel<4> : dlogf_kernel<kRunHeld>),
+                       dim3(a.B * a.H), dim3(kScanThreads), 0, s, a.rowsum, a.colsum, a.dlog_f, a.L);
     e = hipGetLastError();
     trace_end(ACP_K_DLOGF, s);
     return e;

@@ -1,7 +1,7 @@
 """The per-head scans where a thread's run of positions is longer than its
 registers hold and ends inside a batch: the decoding set-up on prompts that are
-no multiple of 4 (single loads) and of 4 only, and dlog f at L = 16448, against
-the oracle (tolerances of test_gpu_decode.py and test_gpu_attn.py)."""
+no multiple of 4 (single loads) and of 4 only, and dlog f at L = 16448; and on both
+sides of 4096, where dlog f holds 4 values per thread or 16; against the oracle (tolerances of test_gpu_decode.py and test_gpu_attn.py)."""
 import pytest
 
 from paper_2504_06949_amd import workloads
@@ -28,7 +28,8 @@ def test_decode_setup_long_odd_prompts(L0, C, sigma):
     _check(w, L0, C, EPS, 2 * L0)
 
 
-def test_dlogf_run_tail():
-    w = workloads.custom("tail", 1, 1, 16448, 64, "bf16", 96, mu=(4.0,))
+@pytest.mark.parametrize("L", [4096, 4160, 16448])
+def test_dlogf_run_tail(L):
+    w = workloads.custom(f"tail{L}", 1, 1, L, 64, "bf16", 96, mu=(4.0,))
     print(f"case: fwd/bwd {w.describe()}", flush=True)
     _full_parity(w)

@@ -119,6 +119,7 @@ __device__ __forceinline__ void col_product(const ColOp<D>& x, const f32x4& p, f
 template <int D, typename Keep>
 __device__ __forceinline__ void add_nonfinite(const float* __restrict__ x, const f32x4& p, f32x4* acc,
                                               int g, int r, Keep keep) {
+#pragma unroll 1
     for (int row = 0; row < 16; ++row) {
         const int src = 16 * (row >> 2) + r;
         float pr = __shfl(p[0], src);
@@ -393,6 +394,8 @@ void dq_f32_kernel(
     }
     for (; kt < kend; kt += kF32Waves) {
         rows_of(kt);
+        // (at d = 128 loaded last: next to the other operands it would cost a wave per SIMD)
+        if constexpr (D == 64) kc.load(Kh + (size_t)16 * kt * D, g, r);
         const f32x4 cj = ld4(ch + 16 * kt + 4 * g);
         f32x4 ds[T];
         bool odd = false;
@@ -411,8 +414,7 @@ void dq_f32_kernel(
                 ds[i] = ds_of(i, p, dp, [&](int t) { return 4 * g + t <= last; });
             }
         }
-        // (loaded last: next to the other operands it would cost a wave per SIMD)
-        kc.load(Kh + (size_t)16 * kt * D, g, r);
+        if constexpr (D == 128) kc.load(Kh + (size_t)16 * kt * D, g, r);
         const bool bad = __ballot(odd) != 0ull && kc.take_nonfinite();
 #pragma unroll
         for (int i = 0; i < T; ++i) {

@@ -108,9 +108,10 @@ __global__ __launch_bounds__(kNormThreads) void rownorm_max_kernel(
 
 // One workgroup of 1024 threads per (batch, head); each thread owns a contiguous
 // run of log f, read and written as float4s (at L = 4096 one per thread, so every
-// access is coalesced), kept in registers up to kRunHeld values and read again in
+// access is coalesced), kept in registers up to kHeld values and read again in
 // batches of that many when it is longer (value by value, each load waited for, a
-// head of 32768 took 64 us).  Three barriers in all, none of which
+// head of 32768 took 64 us).  kHeld is 4, a whole run, up to 4096 gates and kRunHeld beyond
+// (12 heads of 4096: 6.5 us with kRunHeld, 5.9).  Three barriers in all, none of which
 // waits for global stores: one round through LDS carries the scan's wave totals
 // together with every reduction (|log f| sum, last-bit position, flags, norm
 // maxima), one publishes the block corners of c, one the first kept blocks.
@@ -120,6 +121,7 @@ __global__ __launch_bounds__(kNormThreads) void rownorm_max_kernel(
 // by the waves that hold partials.
 constexpr int kWideBit = 1 << 16;   // (inside the kernel only) the gated mode needs pairs
 
+template <int kHeld>
 __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
     const float* __restrict__ log_f, const double* __restrict__ part, int nchunk,
     const float* __restrict__ gamma_q, const float* __restrict__ gamma_k,
@@ -144,7 +146,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
     const int per = run_length(L);
     const bool gated = gate != nullptr;   // c in place: no gates to read or scan
     const int beg = min(t * per, L), n = gated ? 0 : min(beg + per, L) - beg;
-    float xv[kRunHeld];                   // the first batch (all of it if n <= kRunHeld)
+    float xv[kHeld];                   // the first batch (all of it if n <= kHeld)
     load_run(x + beg, 0, n, true, xv);
     double mq = 0.0, mk = 0.0;   // squared norms are >= 0; a NaN wins nan_max
     const bool norms = gamma_q == nullptr;
@@ -189,9 +191,9 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
     } else {
         for (int b = 0;;) {
 #pragma unroll
-            for (int i = 0; i < kRunHeld; ++i)
+            for (int i = 0; i < kHeld; ++i)
                 if (b + i < n) take(xv[i]);
-            b += kRunHeld;
+            b += kHeld;
             if (b >= n) break;
             load_run(x + beg, b, n, true, xv);
         }
@@ -279,10 +281,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
     DD run_dd{0.0, 0.0};
     if (wide) {
         DD l{0.0, 0.0}, la = gate_abs;
-        for (int b = 0; b < n; b += kRunHeld) {
-            if (per > kRunHeld) load_run(x + beg, b, n, true, xv);
+        for (int b = 0; b < n; b += kHeld) {
+            if (per > kHeld) load_run(x + beg, b, n, true, xv);
 #pragma unroll
-            for (int i = 0; i < kRunHeld; ++i) {
+            for (int i = 0; i < kHeld; ++i) {
                 if (b + i < n) {
                     l = dd_add(l, (double)xv[i]);
                     la = dd_add(la, __builtin_fabs((double)xv[i]));
@@ -350,10 +352,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
     };
     // run: the exclusive prefix (float64 or a pair), exact when the span check passes
     auto emit = [&](auto run) __attribute__((always_inline)) {
-        for (int b = 0; b < n; b += kRunHeld) {
-            if (per > kRunHeld) load_run(x + beg, b, n, true, xv);
+        for (int b = 0; b < n; b += kHeld) {
+            if (per > kHeld) load_run(x + beg, b, n, true, xv);
 #pragma unroll
-            for (int i = 0; i < kRunHeld; i += 4) {
+            for (int i = 0; i < kHeld; i += 4) {
                 if (b + i < n) {
                     const int j = beg + b + i;        // a multiple of 4
                     float4 cv;
@@ -465,7 +467,8 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t s) {
         trace_end(ACP_K_ROWNORM, s);
     }
     trace_begin(ACP_K_PLAN, s);
-    hipLaunchKernelGGL(plan_kernel, dim3(BH), dim3(kPlanThreads), 0, s,
+    hipLaunchKernelGGL((a.L <= 4 * kPlanThreads ? plan_kernel<4> : plan_kernel<kRunHeld>), dim3(BH),
+                       dim3(kPlanThreads), 0, s,
                        a.log_f, a.part, a.nchunk, a.gamma_q, a.gamma_k, a.gate, a.H, a.L, a.d,
                        a.log_l_over_eps,
                        a.c, a.u, a.delta, a.row_start, a.col_end, a.kept, a.flags);
